@@ -15,10 +15,9 @@
 // Main loops (each wave owns a sub-tile of 32 x 32 output blocks, each one 32 x 32 or
 // four 16 x 16 MFMA blocks):
 //   bf16: 512 threads = 2 (M) x 4 (N) waves, two per SIMD, so one wave's MFMAs issue
-//         while the other waits on LDS or issues its loads; v_mfma_f32_32x32x16_bf16
-//         for 256 x 256 and 256 x 224 tiles, v_mfma_f32_16x16x32_bf16 for 128 x 256,
-//         256 x 128 and 128 x 128 (the chip holds a higher clock with it, and these
-//         tiles have the registers for its twice as many fragments);
+//         while the other waits on LDS or issues its loads (256 x 256 tiles: in strict
+//         turns, Bf16PingPong); v_mfma_f32_16x16x32_bf16 (the chip holds a higher clock
+//         with it), v_mfma_f32_32x32x16_bf16 for 256 x 224 tiles;
 //         tiles stream HBM -> LDS with buffer_load ... lds (no register staging)
 //         through a ring of K stages: two for 256 x 256 tiles, three for the smaller
 //         tiles, whose stages take fewer MFMAs to consume than a load takes to land;
@@ -293,6 +292,8 @@ struct Bf16Loop {
   //   32 x 32 x 16: row lane % 32, columns 4 (lane / 32) + 8 q + 0..3;
   //   16 x 16 x 32: the block is four 16 x 16 blocks, run q = 2 bi + bj; row
   //                 16 bi + lane % 16, columns 16 bj + 4 (lane / 16) + 0..3.
+  __device__ static int wave_row(int wave) { return wave % WAVES_M * WTM; }
+  __device__ static int wave_col(int wave) { return wave / WAVES_M * WTN; }
   __device__ static int lane_row(int lane) { return MF == 32 ? (lane & 31) : (lane & 15); }
   __device__ static int lane_col(int lane) { return MF == 32 ? 4 * (lane >> 5) : 4 * (lane >> 4); }
   static constexpr int run_row(int i, int q) { return MF == 32 ? 32 * i : 32 * i + 16 * (q >> 1); }
@@ -448,6 +449,173 @@ struct Bf16Loop {
 };
 
 // ---------------------------------------------------------------------------------
+// bf16 main loop of 256 x 256 tiles: two wave groups in turn
+// ---------------------------------------------------------------------------------
+// Wave w shares its SIMD with wave w ^ 4, and the two halves of the workgroup (waves 0-3,
+// rows 0-127; waves 4-7, rows 128-255) run half a phase apart: while one group's waves
+// issue 32 MFMAs back to back, the other's read their next fragments from LDS and issue
+// their DMA loads, and a barrier swaps the roles. The matrix cores then never wait for an
+// LDS read, and the fragments need no second register set, so the 16 x 16 x 32 MFMAs fit
+// (128 accumulator and 64 fragment registers).
+// A K step is two phases: phase 0 multiplies the first 64 rows of the wave's 128 x 64
+// sub-tile, phase 1 the last 64. Each operand's stage is cut in halves that are consumed
+// by one phase (A) or read in phase 0 and kept (B), so a half is loaded again as soon as
+// both groups have read it: three phases, about 3400 cycles, before its next use.
+// Buffers: [stage parity][A0, A1, B0, B1], 16 KiB each. Per wave and half two loads;
+// loads past the last K step get an offset past the resource's end (nothing is fetched,
+// the LDS half takes zeros that nobody reads), so the counted waits hold on every trip.
+// Both waits leave the newest 8 loads in flight:
+//   phase 0 of step t issues A1(t + 1) and needs A1(t), which 6 + 2 loads follow;
+//   phase 1 of step t issues A0, B0, B1 (t + 2) and needs A0, B0, B1 (t + 1): 2 + 6.
+// Bound: the chip's power. A step takes about 2400 cycles for 2048 of MFMA issue (2600
+// with all eight waves in step, 2x2 halves per phase; 2570 with a plain double buffer
+// and 32 x 32 x 16 MFMAs), and the clock falls to 1.6-1.7 GHz as the utilisation rises.
+// 16384 x 3584 x 8192: 835 -> 722 us (1152 -> 1333 TFLOP/s); 8192 x 8192 x 8192: 974 ->
+// 857; 8192 x 1792 x 4096: 121 -> 114; 8192 x 2048 x 8192: 228 -> 212 us. Four phases of 16
+// MFMAs per step, the halves loaded one per phase: 732, 1053, 115 and 217 us.
+struct Bf16PingPong {
+  static constexpr int BM = 256, BN = 256, BK = 64, IN_BYTES = 2, MF = 16;
+  static constexpr int WAVES = 8, THREADS = 512, MI = 4, NI = 2;
+  static constexpr int ROWB = 128;            // bytes per LDS row (64 bf16)
+  static constexpr int HALF = 128 * ROWB;     // half of one operand's stage: 128 rows
+  static constexpr int STAGE = 4 * HALF;      // A0, A1, B0, B1
+  static constexpr int LDS_BYTES = 2 * STAGE;
+  static constexpr int A0 = 0, A1 = 1, B0 = 2, B1 = 3;
+
+  // LDS swizzle and output layout as Bf16Loop's with 16 x 16 x 32 MFMAs
+  __device__ static int swz(int r) { return (r & 7) ^ ((r >> 3) & 1); }
+  __device__ static int wave_row(int wave) { return (wave >> 2) * 128; }
+  __device__ static int wave_col(int wave) { return (wave & 3) * 64; }
+  __device__ static int lane_row(int lane) { return lane & 15; }
+  __device__ static int lane_col(int lane) { return 4 * (lane >> 4); }
+  static constexpr int run_row(int i, int q) { return 32 * i + 16 * (q >> 1); }
+  static constexpr int run_col(int j, int q) { return 32 * j + 16 * (q & 1); }
+
+  // Compiler memory barrier included: no LDS read or DMA load moves across.
+  __device__ __forceinline__ static void barrier() { asm volatile("s_barrier" ::: "memory"); }
+
+  __device__ static void run(unsigned char* lds, const TileGeom& g, f32x16 (&acc)[MI][NI], int wave, int lane) {
+    const __amdgpu_buffer_rsrc_t rsA = make_rsrc(g.Ab, g.abytes);
+    const __amdgpu_buffer_rsrc_t rsB = make_rsrc(g.Bb, g.bbytes);
+    const int nk = g.nk;
+    const uint32_t lds_base =
+        __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_ptr_t)lds)));
+    const uint32_t row_b = static_cast<uint32_t>(g.K) * 2;  // bytes per row of A and B
+    const int lr = lane >> 3;
+    // half i of A: rows 128 w + 64 i .. + 63 of wave groups w = 0, 1; half j of B: columns
+    // 64 w + 32 j .. + 31 of wave columns w = 0 .. 3. Wave w loads rows 16 w .. + 15 of a half.
+    const uint32_t sw_even = ((lane & 7) ^ lr) * 16, sw_odd = ((lane & 7) ^ lr ^ 1) * 16;
+    const uint32_t arow = (wave >> 2) * 128 + (wave & 3) * 16 + lr;
+    const uint32_t brow = (wave >> 1) * 64 + (wave & 1) * 16 + lr;
+    const uint32_t va_even = arow * row_b + sw_even, va_odd = (arow + 8) * row_b + sw_odd;
+    const uint32_t vb_even = brow * row_b + sw_even, vb_odd = (brow + 8) * row_b + sw_odd;
+    const uint32_t l_wave = __builtin_amdgcn_readfirstlane(lds_base + wave * 2048);
+    auto issue = [&](int slot, int t) {
+      const uint32_t kb = t < nk ? static_cast<uint32_t>(t) * 128u : 0x7ffffff0u;
+      const uint32_t l0 = l_wave + (t & 1) * STAGE + slot * HALF;
+      if (slot < 2) {
+        const uint32_t off = kb + ((slot & 1) ? 64 * row_b : 0u);
+        dma16(rsA, l0, va_even, off);
+        dma16(rsA, l0 + 1024, va_odd, off);
+      } else {
+        const uint32_t off = kb + ((slot & 1) ? 32 * row_b : 0u);
+        dma16(rsB, l0, vb_even, off);
+        dma16(rsB, l0 + 1024, vb_odd, off);
+      }
+    };
+    const int lrow = lane & 15, lk = lane >> 4, sw = swz(lrow);
+    const int grp = wave >> 2;
+    uint32_t ab[2], bb[2];  // fragment addresses by k sub-step, in the stage read next
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      const uint32_t vec = ((4 * ks + lk) ^ sw) * 16;
+      ab[ks] = lds_base + (grp * 64 + lrow) * ROWB + vec;
+      bb[ks] = lds_base + 2 * HALF + ((wave & 3) * 32 + lrow) * ROWB + vec;
+    }
+    typedef const __attribute__((address_space(3))) u16x8* lds_frag_t;
+    auto frag = [&](uint32_t base, int off) -> bf16x8 {
+      return __builtin_bit_cast(bf16x8, *(reinterpret_cast<lds_frag_t>(base + off)));
+    };
+    bf16x8 fa[2][4], fb[2][2][2];  // A: [k sub-step][row block], B: [half][k sub-step][column block]
+    auto read_a = [&](int half) {
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) fa[ks][b] = frag(ab[ks], half * HALF + b * 16 * ROWB);
+    };
+    auto read_b = [&](int half) {
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) fb[half][ks][b] = frag(bb[ks], half * HALF + b * 16 * ROWB);
+    };
+    auto mfmas = [&](int hi, int hj) {
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int bi = 0; bi < 4; ++bi)
+#pragma unroll
+          for (int bj = 0; bj < 2; ++bj) {
+            f32x16& blk = acc[2 * hi + (bi >> 1)][hj];
+            const int e = 4 * (2 * (bi & 1) + bj);
+            f32x4 c = f32x4{blk[e + 0], blk[e + 1], blk[e + 2], blk[e + 3]};
+            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[hj][ks][bj], fa[ks][bi], c, 0, 0, 0);
+            blk[e + 0] = c[0];
+            blk[e + 1] = c[1];
+            blk[e + 2] = c[2];
+            blk[e + 3] = c[3];
+          }
+    };
+    // Ends this group's half of a phase (its reads are complete before the barrier, so the
+    // halves they came from may be loaded again) and runs the phase's MFMAs in the other.
+    auto compute = [&](int hi) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_setprio(1);
+      mfmas(hi, hi);
+      mfmas(hi, 1 - hi);
+      __builtin_amdgcn_s_setprio(0);
+      __builtin_amdgcn_sched_barrier(0);
+      barrier();
+    };
+    issue(A0, 0);
+    issue(B0, 0);
+    issue(B1, 0);
+    issue(A1, 0);
+    issue(A0, 1);
+    issue(B0, 1);
+    issue(B1, 1);
+    wait_dma_keep<8>();
+    __syncthreads();
+    if (grp == 1) barrier();  // half a phase behind
+    for (int t = 0; t < nk; ++t) {
+      read_a(0);
+      read_b(0);
+      read_b(1);
+      issue(A1, t + 1);
+      wait_dma_keep<8>();
+      compute(0);
+      read_a(1);
+      issue(A0, t + 2);
+      issue(B0, t + 2);
+      issue(B1, t + 2);
+      wait_dma_keep<8>();
+      compute(1);
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        ab[ks] ^= STAGE;
+        bb[ks] ^= STAGE;
+      }
+    }
+    wait_dma_all();           // the loads past the last step have written their zeros
+    if (grp == 0) barrier();  // both groups have met the same number of barriers
+    __syncthreads();
+  }
+};
+
+
+// ---------------------------------------------------------------------------------
 // fp32 main loop: register-staged, padded LDS rows, BK = 16
 // ---------------------------------------------------------------------------------
 template <int BM_, int BN_>
@@ -455,6 +623,8 @@ struct F32Loop {
   // output layout: as the bf16 loop's 32 x 32 x 16 one (row lane % 32, runs of four
   // columns at 4 (lane / 32) + 8 q)
   static constexpr int MF = 32;
+  __device__ static int wave_row(int wave) { return wave % WAVES_M * WTM; }
+  __device__ static int wave_col(int wave) { return wave / WAVES_M * WTN; }
   __device__ static int lane_row(int lane) { return lane & 31; }
   __device__ static int lane_col(int lane) { return 4 * (lane >> 5); }
   static constexpr int run_row(int i, int) { return 32 * i; }
@@ -765,7 +935,6 @@ __global__ __launch_bounds__(Loop::THREADS, 1) void chunk_gemm(GemmArgs a) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  const int wm = wave % Loop::WAVES_M, wn = wave / Loop::WAVES_M;
   if (blockIdx.x == 0 && a.next_ticket) {
     // clear the next call's state set (its own prologue, folded into this kernel)
     for (int i = tid; i < a.next_n_slots; i += kThreads) a.next_slot_count[i] = 0u;
@@ -908,8 +1077,8 @@ __global__ __launch_bounds__(Loop::THREADS, 1) void chunk_gemm(GemmArgs a) {
     // the offset of run (i, j, q) is split into a per-lane part (one register), a
     // per-row scalar part (i, q) and a constant that fits the instruction's immediate
     // field (j, q), so no per-run offsets stay live across tiles
-    const int vrow = wm * Loop::WTM + Loop::lane_row(lane);  // row of run (i, q): vrow + run_row(i, q)
-    const int vcol = wn * Loop::WTN + Loop::lane_col(lane);  // column of run (j, q): vcol + run_col(j, q)
+    const int vrow = Loop::wave_row(wave) + Loop::lane_row(lane);  // row of run (i, q): vrow + run_row(i, q)
+    const int vcol = Loop::wave_col(wave) + Loop::lane_col(lane);  // column of run (j, q): vcol + run_col(j, q)
     const int voff_c = (vrow * N32 + vcol) * kOutBytes;
     auto store_run = [&](int r, const f32x4& f) {
       const int i = r / (NI * 4), j = (r / 4) % NI, q = r % 4;
@@ -953,8 +1122,7 @@ __global__ __launch_bounds__(Loop::THREADS, 1) void chunk_gemm(GemmArgs a) {
         __syncthreads();
         skip = __builtin_amdgcn_readfirstlane(s_state) < 0;
         const int64_t prow = td.row_begin - a.own_row0;
-        if constexpr (kOutBf16 && Loop::BM == 256 && Loop::BN == 256 && kThreads == 512 &&
-                      Loop::WAVES_M == 2 && Loop::MI == 4 && Loop::MF == 32) {
+        if constexpr (kOutBf16 && Loop::BM == 256 && Loop::BN == 256 && kThreads == 512) {
           // The peers' partial tiles (256 rows of 512 bytes each) stream through the main
           // loop's LDS in 64-row quarters: quarter k of every peer goes to ring slot k
           // (32 KiB), three quarters in flight while one is added. Each wave stages 8
@@ -962,7 +1130,7 @@ __global__ __launch_bounds__(Loop::THREADS, 1) void chunk_gemm(GemmArgs a) {
           // instruction, four instructions); the 16-byte pieces of row r sit at position
           // (piece ^ (r % 32)), so the 32 rows a read instruction touches fall in
           // distinct bank groups. A quarter's rows belong to the four waves of one M
-          // half (wm = k / 2), which read their two row blocks of it (i = 2 (k % 2) and
+          // half (k / 2), which read their two row blocks of it (i = 2 (k % 2) and
           // 2 (k % 2) + 1) back in the accumulator layout and add them. Peers are added
           // in ascending rank order. Loads past the tile's last row read 0.
           constexpr int kRowB = 512, kQuarterB = 64 * kRowB, kPerUnit = 4;
@@ -1000,13 +1168,13 @@ __global__ __launch_bounds__(Loop::THREADS, 1) void chunk_gemm(GemmArgs a) {
               wait_dma_stages<kPerUnit, 2>(units - 1 - u);
               __syncthreads();  // every wave's share of quarter u is in, quarter u - 1 is read
               if (u + 3 < units) issue_quarter(j + (k + 3) / 4, (k + 3) & 3);
-              if (wm == k / 2) {
+              if (Loop::wave_row(wave) / 128 == k / 2) {
 #pragma unroll
                 for (int r = 0; r < kRuns; ++r) {
                   const int i = r / (NI * 4), jj = (r / 4) % NI, q = r % 4;
                   if (i / 2 != k % 2) continue;
-                  const int row = vrow + 32 * i - 64 * k;  // row inside the quarter
-                  const int colb = (vcol + 32 * jj + 8 * q) * 2;
+                  const int row = vrow + Loop::run_row(i, q) - 64 * k;  // row inside the quarter
+                  const int colb = (vcol + Loop::run_col(jj, q)) * 2;
                   const u32x2 raw = *reinterpret_cast<const u32x2*>(lds + k * kQuarterB + row * kRowB +
                                                                     (((colb >> 4) ^ (row & 31)) << 4) + (colb & 15));
                   acc[i][jj][4 * q + 0] += __builtin_bit_cast(float, raw.x << 16);
@@ -1138,8 +1306,8 @@ __global__ __launch_bounds__(Loop::THREADS, 1) void chunk_gemm(GemmArgs a) {
           // and held in registers across the main loop
           int lw = lane;
           asm volatile("" : "+v"(lw));
-          const int l_row = wm * Loop::WTM + Loop::lane_row(lw);  // the lane's row of run (0, q = 0)
-          const int l_col2 = (wn * Loop::WTN + Loop::lane_col(lw)) * 2;  // its byte in the row, run (0, 0)
+          const int l_row = Loop::wave_row(wave) + Loop::lane_row(lw);  // the lane's row of run (0, q = 0)
+          const int l_col2 = (Loop::wave_col(wave) + Loop::lane_col(lw)) * 2;  // its byte in the row, run (0, 0)
           __syncthreads();  // every wave is done reading LDS
 #pragma unroll
           for (int r = 0; r < kRuns; ++r) {
@@ -1245,7 +1413,7 @@ __global__ __launch_bounds__(kPrologueThreads) void chunk_prologue(PrologueArgs 
 // ---------------------------------------------------------------------------------
 // Variant table
 // ---------------------------------------------------------------------------------
-using LoopBf16_256 = Bf16Loop<256, 256>;
+using LoopBf16_256 = Bf16PingPong;
 // Tiles smaller than 256 x 256 finish a stage's MFMAs sooner than its DMA lands when
 // only one stage is in flight; a ring of three keeps two in flight (48 KiB stages: three
 // fit the 160 KiB of LDS). Their loops issue 16 x 16 x 32 MFMAs.

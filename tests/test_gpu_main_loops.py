@@ -1,0 +1,41 @@
+"""GPU parity of the bf16 main loops at the edges of their pipelines: one K step (the ring
+is never full), two, three and more, slices of a single step, tiles with one valid row or
+a few valid columns. Integer inputs, so every sum is exact in fp32 and the output must
+match the oracle bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2601_20595_amd as csg
+import seeded_inputs as si
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    from gpu_util import bf16_rne_of_f64, out_to_f64, run_ag, run_rs
+
+TILES = [(256, 256)]
+
+
+@pytest.mark.parametrize("tile", TILES, ids=lambda t: "%dx%d" % t)
+@pytest.mark.parametrize("steps,split", [(1, 1), (2, 1), (3, 1), (4, 1), (9, 1), (3, 3), (7, 2)])
+@pytest.mark.parametrize("op", ["ag", "rs"])
+def test_pipeline_edges_bit_exact(tile, steps, split, op):
+    W, r, S, Q = 2, 1, 257, 1                     # 514 rows: the last row tile holds a row or two
+    N, K = 256 + 4, 64 * steps                    # the last column tile holds four columns
+    print("main loop", tile, steps, split, op, flush=True)
+    w = si.Workload(131, "loop", op, M=W * S, N=N, K=K, dtype="bf16", out_dtype="bf16", dist="int", world=W, rank=r,
+                    shard_rows=S, chunks_per_shard=Q, order="ring" if op == "ag" else "rs_ring")
+    d = si.draw(w)
+    chunks, order = oracle.uniform_schedule(W, r, S, Q, w.order)
+    cfg = {"timeout_ms": 1000, "bm": tile[0], "bn": tile[1], "bk": 64, "split_k": split}
+    plan = csg.Plan(op, W * S, N, K, "bf16", "bf16", csg.Schedule.uniform(W, r, S, Q, w.order), cfg=cfg)
+    if op == "ag":
+        c, _ = run_ag(plan, chunks, d.A, d.B, "bf16", repeats=2)
+        R = oracle.ag_gemm(d.A.device_array, d.B.device_array, chunks, order)
+    else:
+        c, _ = run_rs(plan, d.A, d.B, "bf16", repeats=2)
+        R, _, _ = oracle.gemm_rs(d.A.device_array, d.B.device_array, chunks, order)
+    assert np.array_equal(out_to_f64(c, "bf16"), bf16_rne_of_f64(R))
+    plan.close()
