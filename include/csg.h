@@ -119,14 +119,18 @@ typedef struct {
  *                   order = (key, band, n, m)
  *   group_m         band height of intra_order 1 (0 = 8)
  *   tile_dispatch   0 or 1 = workgroups take the next entry of the tile list from an
- *                   atomic ticket; 2 = static: workgroup w takes entries s, s + G, s + 2G,
+ *                   atomic ticket (with num_workgroups 0, a list no longer than the
+ *                   co-resident slots is dealt statically, one entry per workgroup, in an
+ *                   order chosen for the caches); 2 = static: workgroup w takes entries s, s + G, s + 2G,
  *                   ... with s = (w mod 8) * (G / 8) + w / 8 when G is a multiple of 8
  *                   (else s = w), so that the workgroups of one die (the dispatcher
  *                   deals workgroups to the 8 dies round robin) take consecutive entries;
  *                   with a tail split (all-gather and grouped GEMMs) the units of the
  *                   split tail tiles, which end the list, are taken in order from a
  *                   shared ticket by whichever workgroup is free first
- *   num_workgroups  persistent grid size G (0 = one per co-resident slot)
+ *   num_workgroups  persistent grid size G (0 = one per co-resident slot, or fewer where
+ *                   every entry has a workgroup of its own; those that copy chunks, and
+ *                   one that relays the copies' completion to the others, come on top)
  *   copy_engines    SDMA engines the chunk copies are spread over (0 = every engine the
  *                   device offers for device-to-device copies)
  *   timeout_ms      bound on every wait (kernel flag polls, host waits); 0 = 2000

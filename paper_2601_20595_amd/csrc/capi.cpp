@@ -39,6 +39,7 @@
 #include <new>
 #include <string>
 #include <thread>
+#include <utility>
 #include <vector>
 
 #include "csg.h"
@@ -117,18 +118,29 @@ struct csg_plan {
   uint32_t epoch = 0;
   bool kernel_pending[2] = {false, false};  // a kernel was launched with epoch parity i
 
-  // device state
+  // device state; the arrays lie in two allocations, unless their comment says otherwise
+  unsigned char* d_state = nullptr;    // what calls write
+  unsigned char* d_tables = nullptr;   // what they only read
   csg::TileDesc* d_tiles = nullptr;
   int32_t* d_list_ptr = nullptr;
   int32_t* d_list_ids = nullptr;
   int32_t* d_raster = nullptr;
   int32_t* d_need = nullptr;
   int32_t* d_list_begin = nullptr;     // [kXcdLists + 1] per-die sub-list bounds (in units)
-  float* d_ws = nullptr;               // split-K partial sums
+  float* d_ws = nullptr;               // split-K partial sums (own allocation)
   uint32_t* d_slot_count = nullptr;    // split-K finished slices per tile, [2][n_tiles]
   int32_t ws_slices = 0;               // partial-sum buffers of split tiles (0: nothing is split)
   int32_t tail_begin = 0;              // static dispatch: first unit dealt from the shared ticket
-  uint64_t* d_trace = nullptr;         // per-unit trace words (cfg.trace)
+  bool one_shot = false;               // every unit has a workgroup of its own (static slots)
+  int32_t unit_wg0 = 0;                // one-shot: workgroups that only copy or relay, before those of the units
+  // One-shot consumers with slots to spare: workgroup 0 relays the copies' completion
+  // values into words in device memory. n_relay chunks (remote_order), words by call parity.
+  int32_t n_relay = 0;
+  int64_t* d_relay = nullptr;               // [2][n_relay]
+  const int64_t** d_relay_src[2] = {nullptr, nullptr};  // [n_relay] completion values
+  int64_t** d_relay_dst[2] = {nullptr, nullptr};        // [n_relay] relay words
+  const int64_t** d_ready_relay[2] = {nullptr, nullptr};  // [n_chunks] what the units poll
+  uint64_t* d_trace = nullptr;         // per-unit trace words (cfg.trace; own allocation)
   std::vector<csg::TileDesc> units;    // host copy of the execution list
   std::vector<int32_t> unit_raster;    // raster id per execution position
   bool lines_aligned = false;          // every chunk of A starts on a 128-byte line
@@ -201,7 +213,7 @@ struct csg_plan {
   int32_t* d_copy_chunk = nullptr;     // per remote position: chunk id
   int32_t* d_copy_parts = nullptr;     // per remote position: copy items
   uint32_t* d_copy_done = nullptr;     // per remote position: items finished
-  int64_t* d_kready = nullptr;         // per chunk: ready word the copy workgroups clear
+  int64_t* d_kready = nullptr;         // per chunk: ready word the copy workgroups clear (own allocation)
   const int64_t** d_ready_k = nullptr; // per chunk: its ready word (local chunks: d_zero)
   int32_t* d_chunk_sent = nullptr;     // per chunk: 1 if sent (producer)
   csg::CopyState* d_copy_state = nullptr;
@@ -214,6 +226,7 @@ struct csg_plan {
   uint32_t* counters(int set) const { return d_counters + set * n_flags(); }
   uint32_t* ticket(int set) const { return d_ticket + set * csg::kXcdLists; }
   csg::DeviceDiag* diag(int set) const { return d_diag + set; }
+  int64_t* relay(int set) const { return d_relay ? d_relay + static_cast<size_t>(set) * n_relay : nullptr; }
   uint32_t* slot_count(int set) const { return d_slot_count ? d_slot_count + set * map.n_tiles() : nullptr; }
   bool consumer() const { return op == CSG_AG_GEMM || op == CSG_GROUPED_GEMM || attention(); }
   bool attention() const { return attn; }
@@ -245,22 +258,8 @@ void free_plan_device(csg_plan* p) {
       for (hsa_signal_t sgn : sets[k])
         if (sgn.handle) hsa_signal_destroy(sgn);
   p->sdma.close();
-  for (void* ptr : {static_cast<void*>(p->d_tiles), static_cast<void*>(p->d_list_ptr),
-                    static_cast<void*>(p->d_list_ids), static_cast<void*>(p->d_raster), static_cast<void*>(p->d_need),
-                    static_cast<void*>(p->d_list_begin), static_cast<void*>(p->d_ws),
-                    static_cast<void*>(p->d_slot_count), static_cast<void*>(p->d_trace),
-                    static_cast<void*>(p->d_ready[0]), static_cast<void*>(p->d_ready[1]),
-                    static_cast<void*>(p->d_part_ready[0]), static_cast<void*>(p->d_part_ready[1]),
-                    static_cast<void*>(p->d_zero),
-                    static_cast<void*>(p->d_counters), static_cast<void*>(p->d_ticket), static_cast<void*>(p->d_diag),
-                    static_cast<void*>(p->d_scratch), static_cast<void*>(p->d_copy_items),
-                    static_cast<void*>(p->d_copy_chunk), static_cast<void*>(p->d_copy_parts),
-                    static_cast<void*>(p->d_copy_done), static_cast<void*>(p->d_kready),
-                    static_cast<void*>(p->d_ready_k), static_cast<void*>(p->d_chunk_sent),
-                    static_cast<void*>(p->d_copy_state), static_cast<void*>(p->d_release_ticks),
-                    static_cast<void*>(p->d_arrival), static_cast<void*>(p->d_chunk_rows),
-                    static_cast<void*>(p->d_join[0]), static_cast<void*>(p->d_join[1]),
-                    static_cast<void*>(p->d_join_flag)})
+  for (void* ptr : {static_cast<void*>(p->d_state), static_cast<void*>(p->d_tables), static_cast<void*>(p->d_ws),
+                    static_cast<void*>(p->d_trace), static_cast<void*>(p->d_kready)})
     if (ptr) (void)hipFree(ptr);
   if (p->h_out_flags) (void)hipHostFree(p->h_out_flags);
   for (hipEvent_t e : {p->ev_copy_in, p->ev_prologue, p->ev_kernel_done[0], p->ev_kernel_done[1]})
@@ -272,20 +271,42 @@ void free_plan_device(csg_plan* p) {
   if (p->aux) (void)hipStreamDestroy(p->aux);
 }
 
-template <class T>
-csg_status upload(T** dst, const std::vector<T>& src) {
-  const size_t bytes = std::max<size_t>(src.size(), 1) * sizeof(T);
-  CSG_HIP(hipMalloc(reinterpret_cast<void**>(dst), bytes));
-  if (!src.empty()) CSG_HIP(hipMemcpy(*dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice));
-  return CSG_OK;
-}
+// Device arrays of a plan, gathered on the host and put into one allocation by one copy
+// (an allocation and a copy each cost about 10 us, and a plan has some twenty arrays).
+// Arrays added by size alone start as zeros.
+struct Arena {
+  std::vector<unsigned char> image;
+  std::vector<std::pair<void**, size_t>> at;  // where an array's address goes, its offset
+
+  size_t take(size_t bytes) {
+    const size_t off = (image.size() + 255) & ~size_t{255};
+    image.resize(off + std::max<size_t>(bytes, 8));
+    return off;
+  }
+  template <class T>
+  void add(T** dst, const std::vector<T>& src) {
+    const size_t off = take(src.size() * sizeof(T));
+    if (!src.empty()) std::memcpy(image.data() + off, src.data(), src.size() * sizeof(T));
+    at.push_back({reinterpret_cast<void**>(dst), off});
+  }
+  template <class T>
+  void add_zeros(T** dst, size_t bytes) {
+    at.push_back({reinterpret_cast<void**>(dst), take(bytes)});
+  }
+  csg_status commit(unsigned char** base) {
+    CSG_HIP(hipMalloc(reinterpret_cast<void**>(base), std::max<size_t>(image.size(), 8)));
+    if (!image.empty()) CSG_HIP(hipMemcpy(*base, image.data(), image.size(), hipMemcpyHostToDevice));
+    for (const auto& x : at) *x.first = *base + x.second;
+    return CSG_OK;
+  }
+};
 
 int64_t in_bytes(const csg_plan* p) { return p->in_dtype == CSG_BF16 ? 2 : 4; }
 int64_t out_bytes(const csg_plan* p) { return p->out_dtype == CSG_BF16 ? 2 : 4; }
 
 // The join tables of csg_plan_join: per signal set, the completion values of every copy
 // signal the set holds.
-csg_status setup_join(csg_plan* p) {
+csg_status setup_join(csg_plan* p, Arena* tables) {
   for (int set = 0; set < 2; ++set) {
     std::vector<const int64_t*> ptrs;
     for (auto* sets : {p->sig_ready, p->sig_send, p->sig_part})
@@ -296,13 +317,15 @@ csg_status setup_join(csg_plan* p) {
         ptrs.push_back(vp);
       }
     p->n_join[set] = static_cast<int32_t>(ptrs.size());
-    const csg_status st = upload(&p->d_join[set], ptrs);
-    if (st != CSG_OK) return st;
+    tables->add(&p->d_join[set], ptrs);
   }
-  CSG_HIP(hipMalloc(&p->d_join_flag, 4));
-  CSG_HIP(hipMemset(p->d_join_flag, 0, 4));
   return CSG_OK;
 }
+
+// Workgroups go to the dies round robin, so counts are kept multiples of the dies.
+int32_t round_up_dies(int32_t n) { return (n + csg::kXcdLists - 1) / csg::kXcdLists * csg::kXcdLists; }
+// Workgroups a one-shot launch sets aside for `n` copy workgroups.
+int32_t copier_slots(int32_t n) { return round_up_dies(n); }
 
 csg_status setup_device(csg_plan* p) {
   DeviceGuard g(p->device);
@@ -321,8 +344,20 @@ csg_status setup_device(csg_plan* p) {
   eo.tile_dispatch = p->cfg.tile_dispatch;
   eo.grid = p->grid;
   eo.tail_wave = p->cfg.tail_wave;
+  const int32_t copiers = p->kernel_copies() && p->consumer() ? copier_slots(p->copy_workgroups()) : 0;
+  if (p->cfg.num_workgroups == 0) eo.slots = p->grid - copiers;
   csg::ExecTables et;
   csg::build_exec_tables(p->sched, m, eo, &et);
+  if (et.one_shot) {
+    p->one_shot = true;
+    p->unit_wg0 = copiers;
+    const int32_t unit_wgs = round_up_dies(static_cast<int32_t>(et.units.size()));
+    if (p->consumer() && !p->kernel_copies() && !p->remote_order.empty() && unit_wgs + csg::kXcdLists <= p->grid) {
+      p->n_relay = static_cast<int32_t>(p->remote_order.size());
+      p->unit_wg0 = csg::kXcdLists;
+    }
+    p->grid = std::min(p->grid, p->unit_wg0 + unit_wgs);
+  }
   const std::vector<csg::TileDesc>& tiles = et.units;
   const std::vector<int32_t>& lptr = et.list_ptr;
   const std::vector<int32_t>& lids = et.list_ids;
@@ -338,36 +373,41 @@ csg_status setup_device(csg_plan* p) {
   p->n_units = n_units;
   p->lines_aligned = et.lines_aligned;
   csg_status st;
-  if ((st = upload(&p->d_tiles, tiles)) != CSG_OK) return st;
-  if ((st = upload(&p->d_list_ptr, lptr)) != CSG_OK) return st;
-  if ((st = upload(&p->d_list_ids, lids)) != CSG_OK) return st;
-  if ((st = upload(&p->d_raster, raster)) != CSG_OK) return st;
-  if ((st = upload(&p->d_need, need)) != CSG_OK) return st;
-  if ((st = upload(&p->d_list_begin, list_begin)) != CSG_OK) return st;
-  const size_t nflag = static_cast<size_t>(std::max(p->n_chunks(), 1));
-  CSG_HIP(hipMalloc(&p->d_zero, 64));
-  CSG_HIP(hipMemset(p->d_zero, 0, 64));
-  CSG_HIP(hipMalloc(&p->d_counters, 2 * nflag * 4));
-  CSG_HIP(hipMemset(p->d_counters, 0, 2 * nflag * 4));
-  CSG_HIP(hipMalloc(&p->d_ticket, 2 * csg::kXcdLists * 4));
-  CSG_HIP(hipMemset(p->d_ticket, 0, 2 * csg::kXcdLists * 4));
+  Arena state, tables;
+  tables.add(&p->d_tiles, tiles);
+  tables.add(&p->d_list_ptr, lptr);
+  tables.add(&p->d_list_ids, lids);
+  tables.add(&p->d_raster, raster);
+  tables.add(&p->d_need, need);
+  tables.add(&p->d_list_begin, list_begin);
+  const size_t nflag = p->n_flags();
+  state.add_zeros(&p->d_zero, 64);
+  state.add_zeros(&p->d_counters, 2 * nflag * 4);
+  state.add_zeros(&p->d_ticket, 2 * csg::kXcdLists * 4);
+  state.add_zeros(&p->d_diag, 2 * sizeof(csg::DeviceDiag));
+  state.add_zeros(&p->d_scratch, 64);
+  state.add_zeros(&p->d_join_flag, 4);
   if (ws_slices > 0) {
     const size_t ws_bytes = static_cast<size_t>(ws_slices) * p->cfg.bm * p->cfg.bn * sizeof(float);
     CSG_HIP(hipMalloc(&p->d_ws, ws_bytes));
-    CSG_HIP(hipMalloc(&p->d_slot_count, 2 * static_cast<size_t>(n_tiles) * 4));
-    CSG_HIP(hipMemset(p->d_slot_count, 0, 2 * static_cast<size_t>(n_tiles) * 4));
+    state.add_zeros(&p->d_slot_count, 2 * static_cast<size_t>(n_tiles) * 4);
   }
+  if (p->n_relay > 0) state.add_zeros(&p->d_relay, 2 * static_cast<size_t>(p->n_relay) * sizeof(int64_t));
   if (p->cfg.trace) {
     const size_t words = static_cast<size_t>(std::max(n_units, 1)) * csg::kTraceWords;
     CSG_HIP(hipMalloc(&p->d_trace, words * sizeof(uint64_t)));
     CSG_HIP(hipMemset(p->d_trace, 0, words * sizeof(uint64_t)));
   }
-  CSG_HIP(hipMalloc(&p->d_diag, 2 * sizeof(csg::DeviceDiag)));
-  CSG_HIP(hipMemset(p->d_diag, 0, 2 * sizeof(csg::DeviceDiag)));
   CSG_HIP(hipHostMalloc(&p->h_out_flags, nflag * 4, hipHostMallocMapped | hipHostMallocCoherent));
   std::memset(p->h_out_flags, 0, nflag * 4);
   CSG_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(&p->h_out_flags_dev), p->h_out_flags, 0));
-  CSG_HIP(hipMalloc(&p->d_scratch, 64));
+  const size_t n_remote = std::max<size_t>(p->remote_order.size(), 1);
+  if (p->kernel_copies()) {
+    state.add_zeros(&p->d_copy_done, n_remote * 4);
+    state.add_zeros(&p->d_release_ticks, n_remote * 8);
+    state.add_zeros(&p->d_copy_state, sizeof(csg::CopyState));
+  }
+  if ((st = state.commit(&p->d_state)) != CSG_OK) return st;
   if (p->kernel_copies()) {
     // copy items: every remote chunk in arrival (emission) order, cut into slabs of
     // kCopySlab bytes; consumers move A rows staging -> landing, the producer (in
@@ -386,16 +426,11 @@ csg_status setup_device(csg_plan* p) {
       words[cid] = p->d_kready + cid;
     }
     p->n_copy_items = static_cast<int32_t>(items.size());
-    if ((st = upload(&p->d_copy_items, items)) != CSG_OK) return st;
-    if ((st = upload(&p->d_copy_chunk, p->remote_order)) != CSG_OK) return st;
-    if ((st = upload(&p->d_copy_parts, parts)) != CSG_OK) return st;
-    if ((st = upload(&p->d_chunk_sent, sent)) != CSG_OK) return st;
-    if ((st = upload(&p->d_ready_k, words)) != CSG_OK) return st;
-    const size_t n_remote = std::max<size_t>(p->remote_order.size(), 1);
-    CSG_HIP(hipMalloc(&p->d_copy_done, n_remote * 4));
-    CSG_HIP(hipMalloc(&p->d_release_ticks, n_remote * 8));
-    CSG_HIP(hipMalloc(&p->d_copy_state, sizeof(csg::CopyState)));
-    CSG_HIP(hipMemset(p->d_copy_state, 0, sizeof(csg::CopyState)));
+    tables.add(&p->d_copy_items, items);
+    tables.add(&p->d_copy_chunk, p->remote_order);
+    tables.add(&p->d_copy_parts, parts);
+    tables.add(&p->d_chunk_sent, sent);
+    tables.add(&p->d_ready_k, words);
   }
   CSG_HIP(hipDeviceSynchronize());
   std::string err = p->sdma.open(p->device, p->cfg.copy_engines, p->d_scratch, p->d_scratch + 8);
@@ -417,15 +452,30 @@ csg_status setup_device(csg_plan* p) {
   for (int set = 0; set < 2; ++set) {
     std::vector<const int64_t*> ptrs(p->n_chunks(), p->d_zero);  // chunks never copied: ready
     if ((st = make_set(p->sig_ready[set], n_copied, &ptrs, &copied)) != CSG_OK) return st;
-    if ((st = upload(&p->d_ready[set], ptrs)) != CSG_OK) return st;
+    tables.add(&p->d_ready[set], ptrs);
+    if (p->n_relay > 0) {
+      std::vector<const int64_t*> src, polled(p->n_chunks(), p->d_zero);
+      std::vector<int64_t*> dst;
+      for (int32_t i = 0; i < p->n_relay; ++i) {
+        int64_t* word = p->relay(set) + i;
+        src.push_back(ptrs[p->remote_order[i]]);
+        dst.push_back(word);
+        polled[p->remote_order[i]] = word;
+      }
+      tables.add(&p->d_relay_src[set], src);
+      tables.add(&p->d_relay_dst[set], dst);
+      tables.add(&p->d_ready_relay[set], polled);
+    }
     if (p->allreduce()) {
       if ((st = make_set(p->sig_send[set], n_copied, nullptr, nullptr)) != CSG_OK) return st;
       const size_t n_part = static_cast<size_t>(p->ar_peers) * (p->ar_own_rows / p->ar_chunk_rows);
       std::vector<const int64_t*> pp(std::max<size_t>(n_part, 1), p->d_zero);
       if ((st = make_set(p->sig_part[set], n_part, &pp, nullptr)) != CSG_OK) return st;
-      if ((st = upload(&p->d_part_ready[set], pp)) != CSG_OK) return st;
+      tables.add(&p->d_part_ready[set], pp);
     }
   }
+  if ((st = setup_join(p, &tables)) != CSG_OK) return st;
+  if ((st = tables.commit(&p->d_tables)) != CSG_OK) return st;
   CSG_HIP(hipEventCreateWithFlags(&p->ev_copy_in, hipEventDisableTiming));
   CSG_HIP(hipEventCreateWithFlags(&p->ev_prologue, hipEventDisableTiming));
   for (hipEvent_t& e : p->ev_kernel_done) CSG_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
@@ -434,7 +484,6 @@ csg_status setup_device(csg_plan* p) {
     CSG_HIP(hipEventCreate(&p->ev_k1[i]));
   }
   CSG_HIP(hipStreamCreateWithFlags(&p->aux, hipStreamNonBlocking));
-  if ((st = setup_join(p)) != CSG_OK) return st;
   CSG_HIP(hipDeviceSynchronize());
   return CSG_OK;
 }
@@ -562,6 +611,8 @@ csg_status launch_prologue_call(csg_plan* p, csg_mode mode, hipStream_t compute)
   pa.diag = p->diag(set);
   pa.slot_count = p->slot_count(set);
   pa.n_slots = p->ws_slices > 0 ? p->map.n_tiles() : 0;
+  pa.relay = p->relay(set);
+  pa.n_relay = p->n_relay;
   if (p->kernel_copies()) {
     // consumers' remote chunks are not there until the copy workgroups move them;
     // the producer waits for nothing before rewriting C (no copy out reads it later)
@@ -656,10 +707,19 @@ csg_status launch_gemm(csg_plan* p, const void* A, const void* B, void* C, csg_m
     a.next_slot_count = p->slot_count(next);
     a.next_diag = p->diag(next);
     a.next_n_slots = p->ws_slices > 0 ? p->map.n_tiles() : 0;
+    a.next_relay = p->relay(next);
+    a.next_n_relay = p->n_relay;
+  }
+  if (p->n_relay > 0) {
+    a.n_relay = p->n_relay;
+    a.relay_src = p->d_relay_src[set];
+    a.relay_dst = p->d_relay_dst[set];
+    a.ready = p->d_ready_relay[set];
   }
   a.n_chunks = p->n_chunks();
-  a.dynamic_ticket = p->cfg.tile_dispatch == 2 ? 0 : 1;
+  a.dynamic_ticket = p->cfg.tile_dispatch == 2 || p->one_shot ? 0 : 1;
   a.tail_begin = p->tail_begin;
+  a.unit_wg0 = p->unit_wg0;
   // Idle workgroups take other dies' units (split tiles exchange partial sums through
   // memory, so their slices may run on any die).
   a.steal = 1;
@@ -884,21 +944,20 @@ csg_status setup_attn_device(csg_plan* p) {
     rows[2 * c + 1] = static_cast<int32_t>(p->sched.chunks[c].row_end);
   }
   csg_status st;
-  if ((st = upload(&p->d_arrival, p->sched.order)) != CSG_OK) return st;
-  if ((st = upload(&p->d_chunk_rows, rows)) != CSG_OK) return st;
+  Arena state, tables;
+  tables.add(&p->d_arrival, p->sched.order);
+  tables.add(&p->d_chunk_rows, rows);
   const size_t nflag = p->n_flags();
-  CSG_HIP(hipMalloc(&p->d_zero, 64));
-  CSG_HIP(hipMemset(p->d_zero, 0, 64));
-  CSG_HIP(hipMalloc(&p->d_counters, 2 * nflag * 4));
-  CSG_HIP(hipMemset(p->d_counters, 0, 2 * nflag * 4));
-  CSG_HIP(hipMalloc(&p->d_ticket, 2 * csg::kXcdLists * 4));
-  CSG_HIP(hipMemset(p->d_ticket, 0, 2 * csg::kXcdLists * 4));
-  CSG_HIP(hipMalloc(&p->d_diag, 2 * sizeof(csg::DeviceDiag)));
-  CSG_HIP(hipMemset(p->d_diag, 0, 2 * sizeof(csg::DeviceDiag)));
+  state.add_zeros(&p->d_zero, 64);
+  state.add_zeros(&p->d_counters, 2 * nflag * 4);
+  state.add_zeros(&p->d_ticket, 2 * csg::kXcdLists * 4);
+  state.add_zeros(&p->d_diag, 2 * sizeof(csg::DeviceDiag));
+  state.add_zeros(&p->d_scratch, 64);
+  state.add_zeros(&p->d_join_flag, 4);
+  if ((st = state.commit(&p->d_state)) != CSG_OK) return st;
   CSG_HIP(hipHostMalloc(&p->h_out_flags, nflag * 4, hipHostMallocMapped | hipHostMallocCoherent));
   std::memset(p->h_out_flags, 0, nflag * 4);
   CSG_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(&p->h_out_flags_dev), p->h_out_flags, 0));
-  CSG_HIP(hipMalloc(&p->d_scratch, 64));
   CSG_HIP(hipDeviceSynchronize());
   std::string err = p->sdma.open(p->device, p->cfg.copy_engines, p->d_scratch, p->d_scratch + 8);
   if (!err.empty()) return fail(CSG_ERR_HIP, "copy engines: %s", err.c_str());
@@ -912,8 +971,10 @@ csg_status setup_attn_device(csg_plan* p) {
       if (hs != HSA_STATUS_SUCCESS) return fail(CSG_ERR_NOMEM, "copy signal: %s", csg::hsa_error(hs).c_str());
       ptrs[p->remote_order[i]] = vp;
     }
-    if ((st = upload(&p->d_ready[set], ptrs)) != CSG_OK) return st;
+    tables.add(&p->d_ready[set], ptrs);
   }
+  if ((st = setup_join(p, &tables)) != CSG_OK) return st;
+  if ((st = tables.commit(&p->d_tables)) != CSG_OK) return st;
   CSG_HIP(hipEventCreateWithFlags(&p->ev_copy_in, hipEventDisableTiming));
   CSG_HIP(hipEventCreateWithFlags(&p->ev_prologue, hipEventDisableTiming));
   for (hipEvent_t& e : p->ev_kernel_done) CSG_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
@@ -922,7 +983,6 @@ csg_status setup_attn_device(csg_plan* p) {
     CSG_HIP(hipEventCreate(&p->ev_k1[i]));
   }
   CSG_HIP(hipStreamCreateWithFlags(&p->aux, hipStreamNonBlocking));
-  if ((st = setup_join(p)) != CSG_OK) return st;
   CSG_HIP(hipDeviceSynchronize());
   return CSG_OK;
 }
@@ -1093,14 +1153,15 @@ struct NaDevice {
   int32_t grid[4] = {0, 0, 0, 0};  // persistent grid per (input, output) dtype pair
   uint64_t sig = 0;              // signature of the tables in the scratch (0: none)
   std::vector<unsigned char> image;
-  int32_t n_units = 0, n_remote = 0, n_items = 0, n_tiles_n = 0;
-  bool lines_aligned = true;
+  int32_t n_units = 0, n_remote = 0, n_items = 0, n_tiles_n = 0, unit_wg0 = 0;
+  bool lines_aligned = true, one_shot = false;
   uint32_t calls = 0;
 };
 std::mutex g_na_mu;
 NaDevice g_na[64];
 
-uint64_t na_signature(const csg::Schedule& s, int64_t M, int64_t N, int64_t K, csg_dtype in, csg_dtype out) {
+uint64_t na_signature(const csg::Schedule& s, int64_t M, int64_t N, int64_t K, csg_dtype in, csg_dtype out,
+                      int32_t copiers) {
   uint64_t h = 1469598103934665603ull;
   auto mix = [&h](uint64_t v) {
     for (int i = 0; i < 8; ++i) {
@@ -1112,6 +1173,7 @@ uint64_t na_signature(const csg::Schedule& s, int64_t M, int64_t N, int64_t K, c
   mix(static_cast<uint64_t>(N));
   mix(static_cast<uint64_t>(K));
   mix(static_cast<uint64_t>(in) * 16 + static_cast<uint64_t>(out));
+  mix(static_cast<uint64_t>(copiers));
   for (const csg::ChunkDesc& c : s.chunks) {
     mix(static_cast<uint64_t>(c.row_begin));
     mix(static_cast<uint64_t>(c.row_end));
@@ -1494,52 +1556,33 @@ csg_status csg_ag_gemm_noalloc(const csg_schedule* sched, int64_t M, int64_t N, 
   const csg::KernelKey key{bf16 ? csg::InType::BF16 : csg::InType::F32, out_dtype == CSG_BF16, false, bm, bn, bk,
                            false};
   const int kslot = (bf16 ? 0 : 2) + (out_dtype == CSG_BF16 ? 0 : 1);
-  const uint64_t sig = na_signature(s, M, N, K, in_dtype, out_dtype);
+  const int32_t copiers = copier_slots(copy_workgroups);
+  const uint64_t sig = na_signature(s, M, N, K, in_dtype, out_dtype, copiers);
 
   std::lock_guard<std::mutex> lock(g_na_mu);
   NaDevice& nd = g_na[device];
   // ---- the tables of this schedule and shape, on the host (only when they differ from
   //      what the device's scratch holds)
-  std::vector<unsigned char> image;
-  int32_t n_units = 0, n_items = 0, n_tiles_n = 0;
-  bool lines_aligned = true;
+  csg::TileMap map;
+  csg::ExecOptions eo;
+  eo.consumer = true;
+  eo.K = K;
+  eo.in_bytes = ib;
+  eo.bk = bk;
+  csg::ExecTables et;
+  std::vector<csg::CopyItem> items;
+  std::vector<int32_t> parts;
   if (nd.sig != sig) {
-    csg::TileMap map;
     std::string err = csg::build_tile_map(s, M, N, bm, bn, false, {}, &map);
     if (!err.empty()) return fail(CSG_ERR_INVALID, "%s", err.c_str());
-    csg::ExecOptions eo;
-    eo.consumer = true;
-    eo.K = K;
-    eo.in_bytes = ib;
-    eo.bk = bk;
-    csg::ExecTables et;
     csg::build_exec_tables(s, map, eo, &et);
-    std::vector<csg::CopyItem> items;
-    std::vector<int32_t> parts;
     csg::build_copy_items(s, remote, K * ib, kCopySlab, &items, &parts);
-    n_units = static_cast<int32_t>(et.units.size());
-    n_items = static_cast<int32_t>(items.size());
-    if (n_units > kNaMaxUnits || static_cast<int64_t>(et.list_ids.size()) > kNaMaxNnz || n_items > kNaMaxItems)
+    if (static_cast<int64_t>(et.units.size()) > kNaMaxUnits || static_cast<int64_t>(et.list_ids.size()) > kNaMaxNnz ||
+        static_cast<int64_t>(items.size()) > kNaMaxItems)
       return fail(CSG_ERR_UNSUPPORTED,
-                  "%d tiles, %zu tile-chunk pairs and %d copy slabs of 256 KiB exceed the no-alloc scratch "
+                  "%zu tiles, %zu tile-chunk pairs and %zu copy slabs of 256 KiB exceed the no-alloc scratch "
                   "(at most %d, %d and %d)",
-                  n_units, et.list_ids.size(), n_items, kNaMaxUnits, kNaMaxNnz, kNaMaxItems);
-    n_tiles_n = map.n_tiles_n;
-    lines_aligned = et.lines_aligned;
-    image.assign(L.end - L.tables, 0);
-    auto put = [&](size_t at, const void* src, size_t bytes) {
-      if (bytes) std::memcpy(image.data() + (at - L.tables), src, bytes);
-    };
-    put(L.tiles, et.units.data(), et.units.size() * sizeof(csg::TileDesc));
-    put(L.list_ptr, et.list_ptr.data(), et.list_ptr.size() * 4);
-    put(L.list_ids, et.list_ids.data(), et.list_ids.size() * 4);
-    put(L.raster, et.raster.data(), et.raster.size() * 4);
-    put(L.list_begin, et.list_begin.data(), et.list_begin.size() * 4);
-    put(L.need, et.need.data(), et.need.size() * 4);
-    put(L.items, items.data(), items.size() * sizeof(csg::CopyItem));
-    put(L.copy_chunk, remote.data(), remote.size() * 4);
-    put(L.copy_parts, parts.data(), parts.size() * 4);
-    // the ready-value pointers need the device's scratch address: filled in below
+                  et.units.size(), et.list_ids.size(), items.size(), kNaMaxUnits, kNaMaxNnz, kNaMaxItems);
   }
   // ---- the device
   DeviceGuard g(device);
@@ -1556,19 +1599,36 @@ csg_status csg_ag_gemm_noalloc(const csg_schedule* sched, int64_t M, int64_t N, 
   if (!nd.grid[kslot]) CSG_HIP(csg::kernel_grid(key, device, &nd.grid[kslot]));
   hipStream_t stream = static_cast<hipStream_t>(stream_v);
   if (nd.sig != sig) {
+    eo.slots = nd.grid[kslot] - copiers;
+    csg::build_exec_tables(s, map, eo, &et);
+    std::vector<unsigned char> image(L.end - L.tables, 0);
+    auto put = [&](size_t at, const void* src, size_t bytes) {
+      if (bytes) std::memcpy(image.data() + (at - L.tables), src, bytes);
+    };
+    put(L.tiles, et.units.data(), et.units.size() * sizeof(csg::TileDesc));
+    put(L.list_ptr, et.list_ptr.data(), et.list_ptr.size() * 4);
+    put(L.list_ids, et.list_ids.data(), et.list_ids.size() * 4);
+    put(L.raster, et.raster.data(), et.raster.size() * 4);
+    put(L.list_begin, et.list_begin.data(), et.list_begin.size() * 4);
+    put(L.need, et.need.data(), et.need.size() * 4);
+    put(L.items, items.data(), items.size() * sizeof(csg::CopyItem));
+    put(L.copy_chunk, remote.data(), remote.size() * 4);
+    put(L.copy_parts, parts.data(), parts.size() * 4);
     // ready values: a local chunk's is the zero word; a remote chunk's, its ready word
     std::vector<const int64_t*> ready(n_chunks, reinterpret_cast<const int64_t*>(ptr + L.zero));
     for (int32_t cid : remote) ready[cid] = reinterpret_cast<const int64_t*>(ptr + L.kready) + cid;
-    std::memcpy(image.data() + (L.ready - L.tables), ready.data(), ready.size() * sizeof(int64_t*));
+    put(L.ready, ready.data(), ready.size() * sizeof(int64_t*));
     nd.sig = 0;  // the scratch holds no valid tables until the copy below is queued
     CSG_HIP(hipMemcpyAsync(ptr + L.tables, image.data(), image.size(), hipMemcpyHostToDevice, stream));
     nd.image.swap(image);
     nd.sig = sig;
-    nd.n_units = n_units;
+    nd.n_units = static_cast<int32_t>(et.units.size());
     nd.n_remote = static_cast<int32_t>(remote.size());
-    nd.n_items = n_items;
-    nd.n_tiles_n = n_tiles_n;
-    nd.lines_aligned = lines_aligned;
+    nd.n_items = static_cast<int32_t>(items.size());
+    nd.n_tiles_n = map.n_tiles_n;
+    nd.lines_aligned = et.lines_aligned;
+    nd.one_shot = et.one_shot;
+    nd.unit_wg0 = et.one_shot ? copiers : 0;
   }
   nd.calls = nd.calls % 0x3ffffff0u + 1;  // the call number the kernel writes into its consumed words
   const uint32_t epoch = nd.calls;
@@ -1607,11 +1667,12 @@ csg_status csg_ag_gemm_noalloc(const csg_schedule* sched, int64_t M, int64_t N, 
   a.epoch = epoch;
   a.n_tiles = mode == CSG_MODE_COPY_ONLY ? 0 : nd.n_units;
   a.n_chunks = n_chunks;
-  a.dynamic_ticket = 1;
+  a.dynamic_ticket = nd.one_shot ? 0 : 1;
+  a.unit_wg0 = nd.unit_wg0;
   a.steal = 1;
   a.n_tiles_n = mode == CSG_MODE_OVERLAP ? nd.n_tiles_n : 0;
   a.acquire_fresh = (!nd.lines_aligned || reinterpret_cast<uintptr_t>(a_landing) % 128 != 0) ? 1 : 0;
-  int32_t grid = nd.grid[kslot];
+  int32_t grid = nd.one_shot ? std::min(nd.grid[kslot], nd.unit_wg0 + round_up_dies(nd.n_units)) : nd.grid[kslot];
   if (copies && nd.n_items > 0) {
     a.copy_items = reinterpret_cast<const csg::CopyItem*>(ptr + L.items);
     a.n_copy_items = nd.n_items;

@@ -72,24 +72,30 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, in
   return __builtin_amdgcn_make_buffer_rsrc(ub, 0, n, kBufferDword3);
 }
 
-// Waits (thread 0 only) until every listed chunk is ready: consumers, until its copy
-// in has landed; the producer, until the previous call's copy out of its rows has
-// completed. Returns 1 if a chunk was seen ready for the first time in this
+// Waits (wave 0, all lanes) until every chunk listed for the unit is ready: consumers,
+// until its copy in has landed; the producer, until the previous call's copy out of its
+// rows has completed. Returns 1 if a chunk was seen ready for the first time in this
 // workgroup, 0 if all were already known, -1 if the wait gave up (timeout here, or
-// another workgroup's abort).
-__device__ int wait_chunks(const GemmArgs& a, int pos, uint32_t* ready_bits) {
+// another workgroup's abort). A ready value is a load of over a microsecond away, so each
+// lane polls a chunk of its own; polled one after another by one thread, the seven
+// 16-row chunks of a 128-row tile held its unit up for 10 us.
+__device__ int wait_chunks(const GemmArgs& a, int pos, uint32_t* ready_bits, int lane) {
   int fresh = 0;
-  for (int p = a.list_ptr[pos]; p < a.list_ptr[pos + 1]; ++p) {
-    const int c = a.list_ids[p];
+  const int p1 = a.list_ptr[pos + 1];
+  for (int p0 = a.list_ptr[pos]; p0 < p1; p0 += 64) {
+    const bool mine = p0 + lane < p1;
+    const int c = mine ? a.list_ids[p0 + lane] : 0;
     const uint32_t bit = 1u << (c & 31);
-    if (ready_bits[c >> 5] & bit) continue;
-    const uint64_t t0 = wall_clock64();
+    const bool ask = mine && !(ready_bits[c >> 5] & bit);
+    if (__builtin_amdgcn_ballot_w64(ask) == 0) continue;
     const int64_t* rp = a.ready[c];
-    int64_t v = load_ready(rp);
-    while (v != 0) {
+    const uint64_t t0 = wall_clock64();
+    int64_t v = ask ? load_ready(rp) : 0;
+    while (__builtin_amdgcn_ballot_w64(v != 0) != 0) {
       if (load_flag(&a.diag->abort)) return -1;
       if (wall_clock64() - t0 > a.timeout_ticks) {
-        if (atomicCAS(&a.diag->timed_out, 0u, 1u) == 0u) {
+        // the first lane still waiting reports its chunk
+        if (lane == __builtin_ctzll(__builtin_amdgcn_ballot_w64(v != 0)) && atomicCAS(&a.diag->timed_out, 0u, 1u) == 0u) {
           a.diag->chunk = c;
           a.diag->tile = a.raster[pos];
           a.diag->observed = static_cast<uint32_t>(v);
@@ -101,12 +107,51 @@ __device__ int wait_chunks(const GemmArgs& a, int pos, uint32_t* ready_bits) {
       // about 1 us between polls: every waiting workgroup polls words of one page,
       // and faster polling loads that memory channel for no gain
       __builtin_amdgcn_s_sleep(32);
-      v = load_ready(rp);
+      if (v != 0) v = load_ready(rp);
     }
-    ready_bits[c >> 5] |= bit;
+    if (ask) atomicOr(&ready_bits[c >> 5], bit);
     fresh = 1;
   }
   return fresh;
+}
+
+// The relay workgroup: thread i polls the completion values of chunks i, i + kThreads, ...
+// of the relayed list and clears their relay words as they land. The completion values
+// are in host memory, whose reads the device takes one after another (17 ns each): with
+// 224 workgroups polling seven of them each, units started up to 27 us after their
+// chunks had landed; the words in device memory cost about a microsecond. Ends when
+// every chunk has landed, when a wait gave up (the abort flag), or after twice the bound
+// of those waits.
+template <int kThreads>
+__device__ void relay_flags(const GemmArgs& a, int tid) {
+  static_assert(kMaxChunks / kThreads <= 32, "a thread's chunks fit a mask");
+  uint32_t pending = 0;
+  for (int i = tid, j = 0; i < a.n_relay; i += kThreads, ++j) pending |= 1u << j;
+  const uint64_t t0 = wall_clock64();
+  while (pending) {
+    for (uint32_t left = pending; left; left &= left - 1) {
+      const int j = __builtin_ctz(left);
+      if (load_ready(a.relay_src[tid + j * kThreads]) == 0) {
+        __hip_atomic_store(a.relay_dst[tid + j * kThreads], int64_t{0}, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        pending &= ~(1u << j);
+      }
+    }
+    if (load_flag(&a.diag->abort) || wall_clock64() - t0 > 2 * a.timeout_ticks) break;
+    __builtin_amdgcn_s_sleep(8);
+  }
+}
+
+// Counts the unit (wave 0, a chunk per lane) against the chunks it read or wrote; the
+// count that completes a chunk sets its flag to the call number.
+__device__ void count_chunks(const GemmArgs& a, int pos, int lane) {
+  const int p1 = a.list_ptr[pos + 1];
+  for (int p = a.list_ptr[pos] + lane; p < p1; p += 64) {
+    const int c = a.list_ids[p];
+    const uint32_t done =
+        __hip_atomic_fetch_add(a.counters + c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) + 1u;
+    if (done == static_cast<uint32_t>(a.need[c]))
+      __hip_atomic_store(a.out_flags + c, a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
 }
 
 // GEMM + all-reduce (thread 0 only): waits until the other ranks' partial sums of the
@@ -940,6 +985,7 @@ __global__ __launch_bounds__(Loop::THREADS, 1) void chunk_gemm(GemmArgs a) {
     for (int i = tid; i < a.next_n_slots; i += kThreads) a.next_slot_count[i] = 0u;
     for (int c = tid; c < a.n_chunks; c += kThreads) a.next_counters[c] = 0u;
     if (tid < kXcdLists) a.next_ticket[tid] = 0u;
+    for (int i = tid; i < a.next_n_relay; i += kThreads) a.next_relay[i] = 1;
     if (tid == 0) {
       a.next_diag->timed_out = 0u;
       a.next_diag->chunk = -1;
@@ -972,31 +1018,40 @@ __global__ __launch_bounds__(Loop::THREADS, 1) void chunk_gemm(GemmArgs a) {
   // workgroup asks first: a workgroup whose next static entry lies there takes the next
   // one from a shared ticket instead, so those slices start as soon as their chunk
   // lands rather than behind their fixed workgroup's previous tile.
-  const int grid = static_cast<int>(gridDim.x), wg = static_cast<int>(blockIdx.x);
+  const int grid = static_cast<int>(gridDim.x) - a.unit_wg0, wg = static_cast<int>(blockIdx.x) - a.unit_wg0;
+  if (!kProducer && a.n_relay > 0 && blockIdx.x == 0) relay_flags<kThreads>(a, tid);
+  if (wg < 0) return;  // a copy or relay workgroup of a launch whose other workgroups run every unit
   const int slot = grid % kXcdLists == 0 ? (wg % kXcdLists) * (grid / kXcdLists) + wg / kXcdLists : wg;
   int iter = 0;
   for (;; ++iter) {
     __syncthreads();  // everyone is done with s_pos / s_state / LDS of the previous tile
-    if (tid == 0) {
-      int pos = a.dynamic_ticket ? next_tile(a, xcd) : slot + iter * grid;
-      if (!a.dynamic_ticket && a.tail_begin > 0 && pos >= a.tail_begin) {
-        const int t = static_cast<int>(atomicAdd(a.ticket, 1u));
-        pos = t < a.n_tiles - a.tail_begin ? a.tail_begin + t : a.n_tiles;
+    if (wave == 0) {
+      int pos = slot + iter * grid;
+      if (a.dynamic_ticket) {
+        if (lane == 0) pos = next_tile(a, xcd);
+      } else if (a.tail_begin > 0 && pos >= a.tail_begin) {
+        if (lane == 0) {
+          const int t = static_cast<int>(atomicAdd(a.ticket, 1u));
+          pos = t < a.n_tiles - a.tail_begin ? a.tail_begin + t : a.n_tiles;
+        }
       }
+      pos = __builtin_amdgcn_readfirstlane(pos);
       int state = 0;
       if (pos < a.n_tiles) {
         const uint64_t t_take = a.trace ? wall_clock64() : 0;
         if (load_flag(&a.diag->abort)) state = -1;
-        else if (!kProducer) state = wait_chunks(a, pos, ready_bits);
-        if (a.trace) {
+        else if (!kProducer) state = wait_chunks(a, pos, ready_bits, lane);
+        if (a.trace && lane == 0) {
           a.trace[kTraceWords * pos + 0] = t_take;
           a.trace[kTraceWords * pos + 1] = wall_clock64();
           a.trace[kTraceWords * pos + 3] = (static_cast<uint64_t>(xcd) << 32) | blockIdx.x;
           a.trace[kTraceWords * pos + 4] = clock64();
         }
       }
-      s_pos = pos;
-      s_state = state;
+      if (lane == 0) {
+        s_pos = pos;
+        s_state = state;
+      }
     }
     __syncthreads();
     // uniform across the workgroup; readfirstlane lets everything derived from it live in SGPRs
@@ -1043,19 +1098,6 @@ __global__ __launch_bounds__(Loop::THREADS, 1) void chunk_gemm(GemmArgs a) {
 #pragma unroll
       for (int j = 0; j < NI; ++j) acc[i][j] = f32x16{};
     Loop::run(lds, g, acc, wave, lane);
-    if (!kProducer && tid == 0) {
-      // every load of this unit has landed (the main loop ends on a wait and a
-      // barrier): count the unit against the remote chunks it read, and report a
-      // chunk whose last reader this was, so the next call may overwrite its rows
-      for (int p = a.list_ptr[pos]; p < a.list_ptr[pos + 1]; ++p) {
-        const int c = a.list_ids[p];
-        const uint32_t done =
-            __hip_atomic_fetch_add(a.counters + c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) + 1u;
-        if (done == static_cast<uint32_t>(a.need[c]))
-          __hip_atomic_store(a.out_flags + c, a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-      }
-    }
-
     // Output run r = (i * NI + j) * 4 + q of this thread: accumulator elements
     // 4q..4q+3 of block (i, j), i.e. output row (i * 32 + lane % 32) and columns
     // (j * 32 + 8q + 4 * (lane / 32) + 0..3) of the wave's sub-tile.
@@ -1098,7 +1140,10 @@ __global__ __launch_bounds__(Loop::THREADS, 1) void chunk_gemm(GemmArgs a) {
     auto wait_previous_copy_out = [&]() -> bool {
       if constexpr (!kProducer) return true;
       __syncthreads();
-      if (tid == 0) s_state = wait_chunks(a, pos, ready_bits);
+      if (wave == 0) {
+        const int st = wait_chunks(a, pos, ready_bits, lane);
+        if (lane == 0) s_state = st;
+      }
       __syncthreads();
       return __builtin_amdgcn_readfirstlane(s_state) >= 0;
     };
@@ -1369,15 +1414,14 @@ __global__ __launch_bounds__(Loop::THREADS, 1) void chunk_gemm(GemmArgs a) {
         wait_dma_all();
         __syncthreads();
       }
-      if (tid == 0) {
-        for (int p = a.list_ptr[pos]; p < a.list_ptr[pos + 1]; ++p) {
-          const int c = a.list_ids[p];
-          const uint32_t done =
-              __hip_atomic_fetch_add(a.counters + c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) + 1u;
-          if (done == static_cast<uint32_t>(a.need[c]))
-            __hip_atomic_store(a.out_flags + c, a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        }
-      }
+      if (wave == 0) count_chunks(a, pos, lane);
+    }
+    if (!kProducer && wave == 0) {
+      // every load of this unit has landed (the main loop ends on a wait and a barrier):
+      // count the unit against the remote chunks it read, so that the last reader of a
+      // chunk lets the next call overwrite its rows. After the output's stores, which
+      // the counters' round trip would otherwise hold up.
+      count_chunks(a, pos, lane);
     }
     if (a.trace && tid == 0) {
       a.trace[kTraceWords * pos + 2] = wall_clock64();
@@ -1394,6 +1438,7 @@ __global__ __launch_bounds__(kPrologueThreads) void chunk_prologue(PrologueArgs 
     for (int c = tid; c < p.n_chunks; c += blockDim.x) p.counters[c] = 0u;
   if (p.ready_words)
     for (int c = tid; c < p.n_chunks; c += blockDim.x) p.ready_words[c] = p.ready_value;
+  for (int i = tid; i < p.n_relay; i += blockDim.x) p.relay[i] = 1;
   if (p.copy_done)
     for (int i = tid; i < p.n_remote; i += blockDim.x) p.copy_done[i] = 0u;
   if (tid < kXcdLists) p.ticket[tid] = 0u;

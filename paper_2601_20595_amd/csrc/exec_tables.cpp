@@ -2,6 +2,7 @@
 #include "exec_tables.hpp"
 
 #include <algorithm>
+#include <utility>
 
 namespace csg {
 
@@ -88,30 +89,59 @@ void build_exec_tables(const Schedule& s, const TileMap& m, const ExecOptions& o
   ExecTables r;
   r.list_ptr.assign(1, 0);
   std::vector<int32_t> unit_begin(kXcdLists + 1, 0);
-  for (int32_t i = 0, x = 0; i < n_tiles; ++i) {
-    while (x <= kXcdLists && list_begin[x] == i) unit_begin[x++] = static_cast<int32_t>(r.units.size());
-    if (i == tail_tile) r.tail_begin = static_cast<int32_t>(r.units.size());
+  std::vector<int32_t> slot(n_tiles, -1);
+  int64_t n_units = 0;
+  for (int32_t i = 0; i < n_tiles; ++i) {
     const int32_t t = exec_order[i];
+    n_units += tile_split[t];
+    if (tile_split[t] > 1) {
+      slot[t] = r.ws_slices;
+      r.ws_slices += tile_split[t];
+    }
+  }
+  auto add_unit = [&](int32_t t, int32_t sl) {
     const RowTile& rt = m.row_tiles[t / nN];
     const int32_t split = tile_split[t];
-    for (int32_t sl = 0; sl < split; ++sl) {
-      const int32_t k0 = static_cast<int32_t>(static_cast<int64_t>(KT) * sl / split);
-      const int32_t k1 = static_cast<int32_t>(static_cast<int64_t>(KT) * (sl + 1) / split);
-      r.units.push_back({static_cast<int32_t>(rt.row_begin), static_cast<int32_t>(rt.row_end), t % nN, rt.group, k0,
-                         k1, split > 1 ? r.ws_slices : -1, sl | (split << 16)});
-      r.raster.push_back(t);
-      for (int32_t q = m.tile_ptr[t]; q < m.tile_ptr[t + 1]; ++q) {
-        const int32_t c = m.tile_chunks[q];
-        // consumers wait only for chunks that have to arrive; producers signal every chunk
-        if (!o.consumer || !s.chunks[c].is_local) r.list_ids.push_back(c);
-      }
-      r.list_ptr.push_back(static_cast<int32_t>(r.list_ids.size()));
+    const int32_t k0 = static_cast<int32_t>(static_cast<int64_t>(KT) * sl / split);
+    const int32_t k1 = static_cast<int32_t>(static_cast<int64_t>(KT) * (sl + 1) / split);
+    r.units.push_back({static_cast<int32_t>(rt.row_begin), static_cast<int32_t>(rt.row_end), t % nN, rt.group, k0, k1,
+                       slot[t], sl | (split << 16)});
+    r.raster.push_back(t);
+    for (int32_t q = m.tile_ptr[t]; q < m.tile_ptr[t + 1]; ++q) {
+      const int32_t c = m.tile_chunks[q];
+      // consumers wait only for chunks that have to arrive; producers signal every chunk
+      if (!o.consumer || !s.chunks[c].is_local) r.list_ids.push_back(c);
     }
-    if (split > 1) r.ws_slices += split;
+    r.list_ptr.push_back(static_cast<int32_t>(r.list_ids.size()));
+  };
+  if (o.slots > 0 && o.tile_dispatch != 2 && o.tail_wave <= 1 && n_units <= o.slots) {
+    // Every unit has a workgroup of its own and all start together, so the order only
+    // decides which units share a die (consecutive eighths of the list): K-slice by
+    // K-slice, since different slices share no operand, and within a slice column by
+    // column when B is the larger operand, row by row otherwise.
+    r.one_shot = true;
+    const bool by_column = nN >= static_cast<int32_t>(m.row_tiles.size());
+    std::vector<std::pair<int64_t, std::pair<int32_t, int32_t>>> at;
+    for (int32_t t = 0; t < n_tiles; ++t) {
+      const int64_t mt = t / nN, nt = t % nN, g = m.row_tiles[t / nN].group;
+      const int64_t key = by_column ? (g * nN + nt) * static_cast<int64_t>(m.row_tiles.size()) + mt : t;
+      for (int32_t sl = 0; sl < tile_split[t]; ++sl)
+        at.push_back({static_cast<int64_t>(sl) * (int64_t{1} << 48) + key, {t, sl}});
+    }
+    std::sort(at.begin(), at.end());
+    for (const auto& u : at) add_unit(u.second.first, u.second.second);
+    r.list_begin.assign(kXcdLists + 1, static_cast<int32_t>(n_units));
+    r.list_begin[0] = 0;
+  } else {
+    for (int32_t i = 0, x = 0; i < n_tiles; ++i) {
+      while (x <= kXcdLists && list_begin[x] == i) unit_begin[x++] = static_cast<int32_t>(r.units.size());
+      if (i == tail_tile) r.tail_begin = static_cast<int32_t>(r.units.size());
+      for (int32_t sl = 0; sl < tile_split[exec_order[i]]; ++sl) add_unit(exec_order[i], sl);
+    }
+    for (int x = 0; x <= kXcdLists; ++x)
+      if (list_begin[x] == n_tiles) unit_begin[x] = static_cast<int32_t>(r.units.size());
+    r.list_begin = unit_begin;
   }
-  for (int x = 0; x <= kXcdLists; ++x)
-    if (list_begin[x] == n_tiles) unit_begin[x] = static_cast<int32_t>(r.units.size());
-  r.list_begin = unit_begin;
   for (const ChunkDesc& c : s.chunks)
     if ((c.row_begin * o.K * o.in_bytes) % 128 != 0) r.lines_aligned = false;
   // per chunk: tiles that write it (producer), or work units that read it (consumers:

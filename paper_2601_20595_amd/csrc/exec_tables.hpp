@@ -25,6 +25,8 @@ struct ExecOptions {
   int32_t tile_dispatch = 0;  // 2: one plain list (dealt statically, die-major), else per-die sub-lists
   int32_t grid = 0;         // persistent workgroups (round-robin over the dies)
   int32_t tail_wave = 0;    // > 1: K-slices (at most) for each die's last partial wave of tiles
+  int32_t slots = 0;        // co-resident workgroups that take units; when every unit has one of its
+                            // own, units are dealt statically (0: never)
 };
 
 struct ExecTables {
@@ -37,6 +39,7 @@ struct ExecTables {
   int32_t ws_slices = 0;             // partial-sum buffers of split tiles
   int32_t tail_begin = 0;            // static dispatch, consumers: first unit of the trailing
                                      // critical tiles, dealt from a shared ticket (0: none)
+  bool one_shot = false;             // every unit has a workgroup: unit i goes to static slot i
   bool lines_aligned = true;         // every chunk of A starts on a 128-byte line
 };
 

@@ -77,6 +77,15 @@ struct GemmArgs {
   // critical path, which end the list) are taken in order from ticket[0] by whichever
   // workgroup is free first, instead of by a fixed workgroup. 0: every position static.
   int32_t tail_begin;
+  // Static dispatch: workgroups below unit_wg0 take no unit (copy or relay workgroups,
+  // where the rest of the grid has a workgroup for every unit), and slots count from there.
+  int32_t unit_wg0;
+  // Consumers: > 0: workgroup 0 relays the ready values: it alone polls the copies'
+  // completion values (relay_src, one per chunk to relay) and clears the words that the
+  // other workgroups poll (relay_dst, which `ready` points at).
+  int32_t n_relay;
+  const int64_t* const* relay_src;
+  int64_t* const* relay_dst;
   // Consumers: 1 if a cache line of A may hold rows of two chunks (a chunk boundary
   // or the buffer start not on a 128-byte line), so a line cached while one chunk was
   // ready could hold stale rows of the next; then a workgroup drops its caches when
@@ -134,6 +143,8 @@ struct GemmArgs {
   uint32_t* next_slot_count;
   DeviceDiag* next_diag;
   int32_t next_n_slots;
+  int64_t* next_relay;       // relay words of the next call's set, set to 1 (null: none)
+  int32_t next_n_relay;
 };
 
 // Everything the per-call prologue resets.
@@ -150,6 +161,8 @@ struct PrologueArgs {
   uint32_t* copy_done;    // per remote position, cleared
   int32_t n_remote;
   CopyState* copy_state;  // its t0 set to the prologue's wall clock
+  int64_t* relay;         // relay words, set to 1 (null: none)
+  int32_t n_relay;
 };
 
 constexpr int kTraceWords = 6;
