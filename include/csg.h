@@ -111,7 +111,11 @@ typedef struct {
  *                   (bk = 64 for bf16, 16 for fp32): bf16 inputs 256 x 256 (every operation;
  *                   the default), 256 x 224 (all-gather and grouped GEMMs), 128 x 256
  *                   (those and GEMM + reduce-scatter, bf16 output), 256 x 128 and 128 x 128
- *                   (all-gather and grouped GEMMs, bf16 output); fp32 inputs 64 x 64
+ *                   (all-gather and grouped GEMMs, bf16 output); fp32 inputs 64 x 64. A bf16
+ *                   plan that names neither bm nor bn, tail split, tail_wave nor
+ *                   num_workgroups keeps 256 x 256 as its tile (the map, the tile list, the
+ *                   ids in traces and diagnostics), and where such tiles would leave most
+ *                   CUs idle its kernel runs each tile as several smaller ones
  *   intra_order     tile order inside a chunk (Section 5.2, intra-chunk swizzle), the
  *                   chunk order staying as it is: 0 = raster (m, n), the local kernel's
  *                   own traversal; 1 = the row tiles sharing a chunk key, ascending, are
@@ -134,7 +138,8 @@ typedef struct {
  *   copy_engines    SDMA engines the chunk copies are spread over (0 = every engine the
  *                   device offers for device-to-device copies)
  *   timeout_ms      bound on every wait (kernel flag polls, host waits); 0 = 2000
- *   split_k         K-slices per tile (0 or 1 = none): the slices of a tile run on different
+ *   split_k         K-slices per tile (0 = none, or the library's choice, by the shape
+ *                   alone, where whole tiles would leave CUs idle; 1 = none): the slices of a tile run on different
  *                   workgroups and the last one to finish adds the fp32 partial sums in slice
  *                   order, so the result depends on split_k but not on timing; a larger value
  *                   shortens the work left after the last chunk lands (and the first emission)
@@ -353,7 +358,7 @@ csg_status csg_ag_gemm(csg_plan* p, void* a_landing, const void* a_staging, cons
  * csg_plan_cfg.copy_backend = CSG_COPY_KERNEL; no copy engine, no signal), without a
  * plan: every table it needs (work units, chunk lists, copy slabs) and every per-call
  * word (tickets, counters, ready words, diagnostics) lives in a static device array of
- * the library, 2 MiB per device, which each device the library runs on holds from the
+ * the library, 18 MiB per device, which each device the library runs on holds from the
  * library's load until the process ends. The call allocates nothing (no hipMalloc,
  * hipFree or allocating library routine); it queues a table upload when the schedule,
  * shape or dtypes differ from the previous call's on the device, then a prologue and
@@ -361,8 +366,9 @@ csg_status csg_ag_gemm(csg_plan* p, void* a_landing, const void* a_staging, cons
  * Arguments as for csg_plan_create + csg_ag_gemm: `s` (host; not kept after the call)
  * covers exactly M rows; a_landing (M x K, local rows in place), a_staging (same
  * layout, the remote rows), b_nk (N x K), c (M x N) are device buffers of `device`,
- * 16-byte aligned; tiles are 256 x 256 x 64 (bf16 input) or 64 x 64 x 16 (f32), dispatched
- * per die with stealing, not split. copy_workgroups: workgroups that move the chunks
+ * 16-byte aligned; tiles are 256 x 256 x 64 (bf16 input; smaller ones and K-slices where
+ * those would leave CUs idle, as for a plan) or 64 x 64 x 16 (f32), dispatched per die with
+ * stealing. copy_workgroups: workgroups that move the chunks
  * (0 = 16). Modes as for csg_ag_gemm (compute-only: a_landing already holds every row;
  * copy-only: the copy workgroups alone run).
  * Limits: at most 4096 chunks, 16384 tiles, 32768 (tile, remote chunk) pairs and 16384

@@ -110,6 +110,11 @@ struct csg_plan {
   std::vector<int64_t> group_rows;
   csg_plan_cfg cfg{};
   csg::TileMap map;
+  // What the kernel runs: the plan's own tiles (kmap a copy of map), or smaller ones and
+  // K-slices the library chose for a plan that names neither (choose_geometry).
+  csg::TileMap kmap;
+  int32_t kbm = 0, kbn = 0, ksplit = 1;
+  std::vector<int32_t> map_raster;     // raster id in map of each kmap tile
   int device = -1;
   csg::KernelKey key{};
   int32_t grid = 0;
@@ -227,7 +232,7 @@ struct csg_plan {
   uint32_t* ticket(int set) const { return d_ticket + set * csg::kXcdLists; }
   csg::DeviceDiag* diag(int set) const { return d_diag + set; }
   int64_t* relay(int set) const { return d_relay ? d_relay + static_cast<size_t>(set) * n_relay : nullptr; }
-  uint32_t* slot_count(int set) const { return d_slot_count ? d_slot_count + set * map.n_tiles() : nullptr; }
+  uint32_t* slot_count(int set) const { return d_slot_count ? d_slot_count + set * kmap.n_tiles() : nullptr; }
   bool consumer() const { return op == CSG_AG_GEMM || op == CSG_GROUPED_GEMM || attention(); }
   bool attention() const { return attn; }
   // ring attention: copies per chunk (keys and values), both completing its signal
@@ -322,6 +327,22 @@ csg_status setup_join(csg_plan* p, Arena* tables) {
   return CSG_OK;
 }
 
+// Per tile of `fine`, the raster id of the tile of `coarse` that holds its first element
+// (both maps of the same rows and columns).
+std::vector<int32_t> containing_tiles(const csg::TileMap& fine, int32_t fine_bn, const csg::TileMap& coarse,
+                                      int32_t coarse_bn) {
+  std::vector<int32_t> r;
+  r.reserve(static_cast<size_t>(fine.n_tiles()));
+  size_t mc = 0;
+  for (const csg::RowTile& rt : fine.row_tiles) {
+    while (coarse.row_tiles[mc].row_end <= rt.row_begin) ++mc;
+    for (int32_t n = 0; n < fine.n_tiles_n; ++n)
+      r.push_back(static_cast<int32_t>(mc) * coarse.n_tiles_n +
+                  static_cast<int32_t>(static_cast<int64_t>(n) * fine_bn / coarse_bn));
+  }
+  return r;
+}
+
 // Workgroups go to the dies round robin, so counts are kept multiples of the dies.
 int32_t round_up_dies(int32_t n) { return (n + csg::kXcdLists - 1) / csg::kXcdLists * csg::kXcdLists; }
 // Workgroups a one-shot launch sets aside for `n` copy workgroups.
@@ -330,14 +351,14 @@ int32_t copier_slots(int32_t n) { return round_up_dies(n); }
 csg_status setup_device(csg_plan* p) {
   DeviceGuard g(p->device);
   if (g.err != hipSuccess) return hip_fail(g.err, "hipSetDevice");
-  const csg::TileMap& m = p->map;
+  const csg::TileMap& m = p->kmap;
   const int32_t n_tiles = m.n_tiles();
   csg::ExecOptions eo;
   eo.consumer = p->consumer();
   eo.K = p->K;
   eo.in_bytes = in_bytes(p);
   eo.bk = p->cfg.bk;
-  eo.split_k = p->cfg.split_k;
+  eo.split_k = p->ksplit;
   eo.tail_split = p->cfg.tail_split;
   eo.tail_chunks = p->cfg.tail_chunks;
   eo.tail_taper = p->cfg.tail_taper;
@@ -369,7 +390,8 @@ csg_status setup_device(csg_plan* p) {
   p->ws_slices = ws_slices;
   p->tail_begin = et.tail_begin;
   p->units = tiles;
-  p->unit_raster = raster;
+  p->unit_raster.clear();
+  for (int32_t x : raster) p->unit_raster.push_back(p->map_raster[x]);
   p->n_units = n_units;
   p->lines_aligned = et.lines_aligned;
   csg_status st;
@@ -388,7 +410,7 @@ csg_status setup_device(csg_plan* p) {
   state.add_zeros(&p->d_scratch, 64);
   state.add_zeros(&p->d_join_flag, 4);
   if (ws_slices > 0) {
-    const size_t ws_bytes = static_cast<size_t>(ws_slices) * p->cfg.bm * p->cfg.bn * sizeof(float);
+    const size_t ws_bytes = static_cast<size_t>(ws_slices) * p->kbm * p->kbn * sizeof(float);
     CSG_HIP(hipMalloc(&p->d_ws, ws_bytes));
     state.add_zeros(&p->d_slot_count, 2 * static_cast<size_t>(n_tiles) * 4);
   }
@@ -610,7 +632,7 @@ csg_status launch_prologue_call(csg_plan* p, csg_mode mode, hipStream_t compute)
   pa.ticket = p->ticket(set);
   pa.diag = p->diag(set);
   pa.slot_count = p->slot_count(set);
-  pa.n_slots = p->ws_slices > 0 ? p->map.n_tiles() : 0;
+  pa.n_slots = p->ws_slices > 0 ? p->kmap.n_tiles() : 0;
   pa.relay = p->relay(set);
   pa.n_relay = p->n_relay;
   if (p->kernel_copies()) {
@@ -706,7 +728,7 @@ csg_status launch_gemm(csg_plan* p, const void* A, const void* B, void* C, csg_m
     a.next_counters = p->counters(next);
     a.next_slot_count = p->slot_count(next);
     a.next_diag = p->diag(next);
-    a.next_n_slots = p->ws_slices > 0 ? p->map.n_tiles() : 0;
+    a.next_n_slots = p->ws_slices > 0 ? p->kmap.n_tiles() : 0;
     a.next_relay = p->relay(next);
     a.next_n_relay = p->n_relay;
   }
@@ -726,7 +748,7 @@ csg_status launch_gemm(csg_plan* p, const void* A, const void* B, void* C, csg_m
   a.trace = p->d_trace;
   // only copies of this call leave rows fresh in HBM; without them the warm-up loads
   // would only cost time
-  a.n_tiles_n = (p->consumer() && mode == CSG_MODE_OVERLAP && p->cfg.warm_rows != 2) ? p->map.n_tiles_n : 0;
+  a.n_tiles_n = (p->consumer() && mode == CSG_MODE_OVERLAP && p->cfg.warm_rows != 2) ? p->kmap.n_tiles_n : 0;
   a.acquire_fresh = (p->consumer() && (!p->lines_aligned || reinterpret_cast<uintptr_t>(A) % 128 != 0)) ? 1 : 0;
   int32_t grid = p->grid;
   if (kc) {
@@ -1107,12 +1129,15 @@ constexpr int32_t kNaMaxChunks = 4096;   // also the kernels' ready-bitmap bound
 constexpr int32_t kNaMaxUnits = 16384;   // tiles
 constexpr int32_t kNaMaxNnz = 32768;     // (tile, remote chunk) pairs
 constexpr int32_t kNaMaxItems = 16384;   // 256 KiB copy slabs: 4 GiB of remote rows
+constexpr int32_t kNaMaxSplitTiles = 256;            // tiles of a split launch
+constexpr int64_t kNaWorkspace = int64_t{16} << 20;  // its partial sums
 
 struct NaLayout {
   // per-call words, reset by the prologue of every call
-  size_t diag, ticket, copy_state, counters, out_flags, kready, copy_done;
+  size_t diag, ticket, copy_state, counters, out_flags, kready, copy_done, slot_count;
   // tables, written when a call's schedule or shape differs from the previous call's
   size_t tables, zero, tiles, list_ptr, list_ids, raster, list_begin, need, ready, items, copy_chunk, copy_parts;
+  size_t ws;  // partial sums of split tiles
   size_t end;
 };
 
@@ -1131,6 +1156,7 @@ NaLayout na_layout() {
   L.out_flags = take(kNaMaxChunks * 4);
   L.kready = take(kNaMaxChunks * 8);
   L.copy_done = take(kNaMaxChunks * 4);
+  L.slot_count = take(kNaMaxSplitTiles * 4);
   L.tables = o;
   L.zero = take(64);
   L.tiles = take(kNaMaxUnits * sizeof(csg::TileDesc));
@@ -1143,6 +1169,8 @@ NaLayout na_layout() {
   L.items = take(kNaMaxItems * sizeof(csg::CopyItem));
   L.copy_chunk = take(kNaMaxChunks * 4);
   L.copy_parts = take(kNaMaxChunks * 4);
+  L.ws = o;
+  take(kNaWorkspace);
   L.end = o;
   return L;
 }
@@ -1153,7 +1181,9 @@ struct NaDevice {
   int32_t grid[4] = {0, 0, 0, 0};  // persistent grid per (input, output) dtype pair
   uint64_t sig = 0;              // signature of the tables in the scratch (0: none)
   std::vector<unsigned char> image;
-  int32_t n_units = 0, n_remote = 0, n_items = 0, n_tiles_n = 0, unit_wg0 = 0;
+  int32_t n_units = 0, n_remote = 0, n_items = 0, n_tiles_n = 0, unit_wg0 = 0, n_split_tiles = 0;
+  csg::KernelKey key{};          // the kernel the tables are for, and its persistent grid
+  int32_t key_grid = 0;
   bool lines_aligned = true, one_shot = false;
   uint32_t calls = 0;
 };
@@ -1308,6 +1338,7 @@ csg_status csg_plan_create(csg_op op, int64_t M, int64_t N, int64_t K, csg_dtype
   }
   csg_plan_cfg c = cfg ? *cfg : csg_plan_cfg{};
   const bool bf16 = in_dtype == CSG_BF16;
+  const bool named_tiles = c.bm != 0 || c.bn != 0, free_split = c.split_k == 0;
   if (c.bm == 0) c.bm = bf16 ? 256 : 64;
   if (c.bn == 0) c.bn = bf16 ? 256 : 64;
   if (c.bk == 0) c.bk = bf16 ? 64 : 16;
@@ -1431,6 +1462,27 @@ csg_status csg_plan_create(csg_op op, int64_t M, int64_t N, int64_t K, csg_dtype
     {
       DeviceGuard g(device);
       hipError_t e = g.err != hipSuccess ? g.err : csg::kernel_grid(p->key, device, &p->grid);
+      p->kbm = c.bm;
+      p->kbn = c.bn;
+      p->ksplit = c.split_k;
+      const bool free_tiles = bf16 && !named_tiles && c.tail_split <= 1 && c.tail_wave <= 1 &&
+                              c.split_k <= 1 && c.num_workgroups == 0;
+      if (e == hipSuccess && free_tiles) {
+        const int32_t copiers = p->kernel_copies() && p->consumer() ? copier_slots(c.copy_workgroups) : 0;
+        const csg::Geometry geo =
+            csg::choose_geometry(groups.empty() ? std::vector<int64_t>{M} : groups, N, K, p->grid - copiers,
+                                 p->allreduce() ? 128 : 64, free_split && !p->allreduce(), int64_t{1} << 30);
+        csg::KernelKey key = p->key;
+        key.bm = geo.bm;
+        key.bn = geo.bn;
+        if (geo.bm > 0 && csg::kernel_exists(key)) {
+          p->kbm = geo.bm;
+          p->kbn = geo.bn;
+          if (free_split) p->ksplit = geo.split;
+          p->key = key;
+          e = csg::kernel_grid(key, device, &p->grid);
+        }
+      }
       if (e != hipSuccess) {
         p->device = -1;
         delete p;
@@ -1438,6 +1490,18 @@ csg_status csg_plan_create(csg_op op, int64_t M, int64_t N, int64_t K, csg_dtype
       }
     }
     if (c.num_workgroups > 0) p->grid = c.num_workgroups;
+    if (p->kbm == c.bm && p->kbn == c.bn) {
+      p->kmap = p->map;
+    } else {
+      err = csg::build_tile_map(p->sched, M, N, p->kbm, p->kbn, !p->consumer(), groups, &p->kmap, c.intra_order,
+                                c.group_m);
+      if (!err.empty()) {
+        p->device = -1;
+        delete p;
+        return fail(CSG_ERR_INVALID, "%s", err.c_str());
+      }
+    }
+    p->map_raster = containing_tiles(p->kmap, p->kbn, p->map, c.bn);
     st = setup_device(p);
     if (st != CSG_OK) {
       std::string msg = g_last_error;
@@ -1553,8 +1617,7 @@ csg_status csg_ag_gemm_noalloc(const csg_schedule* sched, int64_t M, int64_t N, 
     return fail(CSG_ERR_INVALID, "buffers must be 16-byte aligned");
   const NaLayout L = na_layout();
   if (L.end > csg::kNoAllocScratchBytes) return fail(CSG_ERR_STATE, "scratch layout exceeds the scratch array");
-  const csg::KernelKey key{bf16 ? csg::InType::BF16 : csg::InType::F32, out_dtype == CSG_BF16, false, bm, bn, bk,
-                           false};
+  csg::KernelKey key{bf16 ? csg::InType::BF16 : csg::InType::F32, out_dtype == CSG_BF16, false, bm, bn, bk, false};
   const int kslot = (bf16 ? 0 : 2) + (out_dtype == CSG_BF16 ? 0 : 1);
   const int32_t copiers = copier_slots(copy_workgroups);
   const uint64_t sig = na_signature(s, M, N, K, in_dtype, out_dtype, copiers);
@@ -1599,9 +1662,32 @@ csg_status csg_ag_gemm_noalloc(const csg_schedule* sched, int64_t M, int64_t N, 
   if (!nd.grid[kslot]) CSG_HIP(csg::kernel_grid(key, device, &nd.grid[kslot]));
   hipStream_t stream = static_cast<hipStream_t>(stream_v);
   if (nd.sig != sig) {
-    eo.slots = nd.grid[kslot] - copiers;
+    int32_t grid = nd.grid[kslot];
+    if (bf16) {
+      // smaller tiles and K-slices for launches that leave CUs idle, where they fit the scratch
+      const csg::Geometry geo = csg::choose_geometry({M}, N, K, grid - copiers, 64, true, kNaWorkspace);
+      csg::KernelKey k2 = key;
+      k2.bm = geo.bm;
+      k2.bn = geo.bn;
+      csg::TileMap m2;
+      csg::ExecOptions e2 = eo;
+      csg::ExecTables t2;
+      if (geo.bm > 0 && (geo.bm != bm || geo.bn != bn || geo.split > 1) && csg::kernel_exists(k2) &&
+          csg::build_tile_map(s, M, N, geo.bm, geo.bn, false, {}, &m2).empty()) {
+        e2.split_k = geo.split;
+        csg::build_exec_tables(s, m2, e2, &t2);
+        if (static_cast<int64_t>(t2.units.size()) <= kNaMaxUnits && static_cast<int64_t>(t2.list_ids.size()) <= kNaMaxNnz &&
+            (t2.ws_slices == 0 || m2.n_tiles() <= kNaMaxSplitTiles)) {
+          CSG_HIP(csg::kernel_grid(k2, device, &grid));
+          key = k2;
+          map = std::move(m2);
+          eo = e2;
+        }
+      }
+    }
+    eo.slots = grid - copiers;
     csg::build_exec_tables(s, map, eo, &et);
-    std::vector<unsigned char> image(L.end - L.tables, 0);
+    std::vector<unsigned char> image(L.ws - L.tables, 0);
     auto put = [&](size_t at, const void* src, size_t bytes) {
       if (bytes) std::memcpy(image.data() + (at - L.tables), src, bytes);
     };
@@ -1627,6 +1713,9 @@ csg_status csg_ag_gemm_noalloc(const csg_schedule* sched, int64_t M, int64_t N, 
     nd.n_items = static_cast<int32_t>(items.size());
     nd.n_tiles_n = map.n_tiles_n;
     nd.lines_aligned = et.lines_aligned;
+    nd.key = key;
+    nd.key_grid = grid;
+    nd.n_split_tiles = et.ws_slices > 0 ? map.n_tiles() : 0;
     nd.one_shot = et.one_shot;
     nd.unit_wg0 = et.one_shot ? copiers : 0;
   }
@@ -1644,6 +1733,8 @@ csg_status csg_ag_gemm_noalloc(const csg_schedule* sched, int64_t M, int64_t N, 
   pa.copy_done = reinterpret_cast<uint32_t*>(ptr + L.copy_done);
   pa.n_remote = nd.n_remote;
   pa.copy_state = reinterpret_cast<csg::CopyState*>(ptr + L.copy_state);
+  pa.slot_count = reinterpret_cast<uint32_t*>(ptr + L.slot_count);
+  pa.n_slots = nd.n_split_tiles;
   CSG_HIP(csg::launch_prologue(pa, stream));
   csg::GemmArgs a{};
   a.A = a_landing;
@@ -1672,7 +1763,9 @@ csg_status csg_ag_gemm_noalloc(const csg_schedule* sched, int64_t M, int64_t N, 
   a.steal = 1;
   a.n_tiles_n = mode == CSG_MODE_OVERLAP ? nd.n_tiles_n : 0;
   a.acquire_fresh = (!nd.lines_aligned || reinterpret_cast<uintptr_t>(a_landing) % 128 != 0) ? 1 : 0;
-  int32_t grid = nd.one_shot ? std::min(nd.grid[kslot], nd.unit_wg0 + round_up_dies(nd.n_units)) : nd.grid[kslot];
+  a.ws = reinterpret_cast<float*>(ptr + L.ws);
+  a.slot_count = pa.slot_count;
+  int32_t grid = nd.one_shot ? std::min(nd.key_grid, nd.unit_wg0 + round_up_dies(nd.n_units)) : nd.key_grid;
   if (copies && nd.n_items > 0) {
     a.copy_items = reinterpret_cast<const csg::CopyItem*>(ptr + L.items);
     a.n_copy_items = nd.n_items;
@@ -1689,7 +1782,7 @@ csg_status csg_ag_gemm_noalloc(const csg_schedule* sched, int64_t M, int64_t N, 
     if (!copies || nd.n_items == 0) return CSG_OK;  // nothing to move
     grid = std::min(copy_workgroups, grid);
   }
-  CSG_HIP(csg::launch_chunk_gemm(key, a, grid, stream, nullptr, nullptr));
+  CSG_HIP(csg::launch_chunk_gemm(nd.key, a, grid, stream, nullptr, nullptr));
   return CSG_OK;
 }
 
@@ -1981,7 +2074,10 @@ csg_status csg_plan_check(csg_plan* p, csg_diag* out) {
     csg::DeviceDiag dd{};
     CSG_HIP(hipMemcpyAsync(&dd, p->diag(p->epoch & 1), sizeof dd, hipMemcpyDeviceToHost, p->aux));
     CSG_HIP(hipStreamSynchronize(p->aux));
-    if (dd.timed_out && !d.timed_out) d = csg_diag{1, dd.chunk, dd.tile, dd.observed, dd.epoch, 0};
+    if (dd.timed_out && !d.timed_out) {
+      const bool known = dd.tile >= 0 && static_cast<size_t>(dd.tile) < p->map_raster.size();
+      d = csg_diag{1, dd.chunk, known ? p->map_raster[dd.tile] : dd.tile, dd.observed, dd.epoch, 0};
+    }
     if (!d.timed_out && p->kernel_pending[p->epoch & 1] && dd.units_done != p->expected_units) {
       if (out) *out = d;
       return fail(CSG_ERR_STATE, "the kernel ran %u of %u work units (a die without workgroups?)", dd.units_done,

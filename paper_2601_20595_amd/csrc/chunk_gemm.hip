@@ -316,8 +316,9 @@ struct Bf16Loop {
   static constexpr int LDS_BYTES = STAGES * STAGE;
   static constexpr int A_GROUPS = BM / 8, B_GROUPS = BN / 8;  // a stage is loaded in groups of 8 rows
   // DMA loads each wave issues per stage, when every wave issues the same number
-  static constexpr bool EVEN_ISSUE = A_GROUPS % (2 * WAVES_M_ * WAVES_N_) == 0 && B_GROUPS % (2 * WAVES_M_ * WAVES_N_) == 0;
-  static constexpr int DMA_PER_STAGE = (A_GROUPS + B_GROUPS) / (WAVES_M_ * WAVES_N_);
+  static constexpr bool even_issue(int groups) { return groups == WAVES || groups % (2 * WAVES) == 0; }
+  static constexpr bool EVEN_ISSUE = even_issue(A_GROUPS) && even_issue(B_GROUPS);
+  static constexpr int DMA_PER_STAGE = (A_GROUPS + B_GROUPS) / WAVES;
   static_assert(WAVES == 8 && BM % 8 == 0 && BN % 8 == 0 && WTM % 32 == 0 && WTN % 32 == 0, "bf16 tile shape");
   static_assert(STAGES == 2 || ((STAGES == 3 || STAGES == 4) && EVEN_ISSUE && (STAGES - 2) * DMA_PER_STAGE < 64),
                 "a deeper ring counts each wave's loads per stage");
@@ -358,6 +359,9 @@ struct Bf16Loop {
       const uint32_t l0 = __builtin_amdgcn_readfirstlane(rows0 + g0 * 8 * ROWB);
 #pragma unroll
       for (int q = 0; q < kPer; ++q) dma16(rs, l0 + q * 8 * ROWB, (q & 1) ? v_odd : v_even, (g0 + q) * 8 * K * 2 + kbase);
+    } else if constexpr (kGroups == WAVES) {
+      const uint32_t l0 = __builtin_amdgcn_readfirstlane(rows0 + wave * 8 * ROWB);
+      dma16(rs, l0, (wave & 1) ? v_odd : v_even, wave * 8 * K * 2 + kbase);
     } else {
       static_assert(kGroups % 2 == 0, "an even number of 8-row groups");
       constexpr int kPairs = kGroups / 2;
@@ -1465,6 +1469,7 @@ using LoopBf16_256 = Bf16PingPong;
 using LoopBf16_256x128 = Bf16Loop<256, 128, 2, 4, 3, 16>;
 using LoopBf16_128x256 = Bf16Loop<128, 256, 2, 4, 3, 16>;
 using LoopBf16_128 = Bf16Loop<128, 128, 2, 4, 3, 16>;
+using LoopBf16_128x64 = Bf16Loop<128, 64, 4, 2, 3, 16>;
 using LoopBf16_256x224 = Bf16Loop<256, 224, 8, 1>;
 using LoopF32_64 = F32Loop<64, 64>;
 
@@ -1493,13 +1498,16 @@ struct Variant {
   int threads;
   hipError_t (*launch)(const GemmArgs&, int32_t, hipStream_t, hipEvent_t, hipEvent_t);
   const void* (*func)();
+  bool internal;  // not a tile shape that a plan's configuration may name
 };
 
-#define CSG_VARIANT(IN, LOOP, OB, PR, RD)                                                                    \
+#define CSG_VARIANT_AS(IN, LOOP, OB, PR, RD, INTERNAL)                                                        \
   Variant {                                                                                                   \
     IN, OB, PR, RD, LOOP::BM, LOOP::BN, LOOP::BK, LOOP::THREADS, &launch_one<LOOP, OB, PR, RD>,               \
-        &kernel_ptr<LOOP, OB, PR, RD>                                                                         \
+        &kernel_ptr<LOOP, OB, PR, RD>, INTERNAL                                                               \
   }
+#define CSG_VARIANT(IN, LOOP, OB, PR, RD) CSG_VARIANT_AS(IN, LOOP, OB, PR, RD, false)
+#define CSG_INTERNAL(IN, LOOP, OB, PR, RD) CSG_VARIANT_AS(IN, LOOP, OB, PR, RD, true)
 
 const Variant kVariants[] = {
     CSG_VARIANT(InType::BF16, LoopBf16_256, true, false, false),  CSG_VARIANT(InType::BF16, LoopBf16_256, true, true, false),
@@ -1519,6 +1527,16 @@ const Variant kVariants[] = {
     // 256 x 224 tiles: N = 7 x 256 and 14 x 256 shapes fill every CU in whole waves
     CSG_VARIANT(InType::BF16, LoopBf16_256x224, true, false, false),
     CSG_VARIANT(InType::BF16, LoopBf16_256x224, false, false, false),
+    // chosen by the library only (choose_geometry), for launches that leave CUs idle
+    CSG_INTERNAL(InType::BF16, LoopBf16_128x64, true, false, false),
+    CSG_INTERNAL(InType::BF16, LoopBf16_128x64, false, false, false),
+    CSG_INTERNAL(InType::BF16, LoopBf16_128x64, true, true, false),
+    CSG_INTERNAL(InType::BF16, LoopBf16_128x64, false, true, false),
+    CSG_INTERNAL(InType::BF16, LoopBf16_128, false, false, false),
+    CSG_INTERNAL(InType::BF16, LoopBf16_128, true, true, false),
+    CSG_INTERNAL(InType::BF16, LoopBf16_128, false, true, false),
+    CSG_INTERNAL(InType::BF16, LoopBf16_128, true, true, true),
+    CSG_INTERNAL(InType::BF16, LoopBf16_128, false, true, true),
 };
 
 const Variant* find_variant(const KernelKey& k) {
@@ -1530,7 +1548,12 @@ const Variant* find_variant(const KernelKey& k) {
 }
 }  // namespace
 
-bool kernel_supported(const KernelKey& key) { return find_variant(key) != nullptr; }
+bool kernel_supported(const KernelKey& key) {
+  const Variant* v = find_variant(key);
+  return v != nullptr && !v->internal;
+}
+
+bool kernel_exists(const KernelKey& key) { return find_variant(key) != nullptr; }
 
 int32_t kernel_max_chunks() { return kMaxChunks; }
 

@@ -154,6 +154,55 @@ void build_exec_tables(const Schedule& s, const TileMap& m, const ExecOptions& o
   *out = std::move(r);
 }
 
+// The estimate, in microseconds, from kernels of M x N x K between 128 x 1792 x 4096 and
+// 4096 x 1792 x 4096 timed with every tile shape and 1 to 16 slices: a launch whose
+// units all have a workgroup takes
+//   start + (K steps per unit) * step + (a slice's share of the reduction, if split).
+// A step of the smaller tiles is bound by LDS reads (816, 1117 cycles); of 256 x 256
+// tiles by the matrix cores, and as more of them run the clock falls. Measured and
+// estimated kernels, us:
+//   128 x 1792 x 4096:  256 x 256 73.8 (79), 128 x 128 35.1 (36), 128 x 64 27.5 (28), in
+//                       four slices 16.8 (17), in eight 17.5 (18)
+//   1200 x 1228 x 2048: 256 x 256 43.0 (44), 128 x 128 22.9 (23), 128 x 64 19.5 (19)
+//   2048 x 1792 x 4096: 256 x 256 77.5 (79), in two slices 58.6 (56), 128 x 128 39.6 (39)
+//   4096 x 1792 x 4096: 256 x 256 79.0 (79), in two slices 69.3 (68); 128 x 128 93.1 (448
+//                       tiles, two waves)
+// 256 x 256 tiles run whole wave after whole wave; the small ones, whose operands cost
+// twice the traffic per product, only where all of them run at once.
+Geometry choose_geometry(const std::vector<int64_t>& group_rows, int64_t N, int64_t K, int32_t slots, int32_t min_bn,
+                         bool may_split, int64_t ws_bytes) {
+  struct Tile {
+    int32_t bm, bn;
+    double start, step, red0, red;
+  };
+  static const Tile kTiles[] = {{256, 256, 10.0, 1.08, 3.0, 4.0}, {128, 128, 8.0, 0.46, 2.0, 1.0},
+                                {128, 64, 6.5, 0.34, 1.0, 0.9}};
+  static const int32_t kSlices[] = {1, 2, 3, 4, 6, 8};
+  const int64_t steps = K / 64;
+  Geometry best;
+  double best_us = 0.0;
+  for (const Tile& x : kTiles) {
+    if (x.bn < min_bn) continue;
+    int64_t tiles = 0;
+    for (int64_t rows : group_rows) tiles += (rows + x.bm - 1) / x.bm;
+    tiles *= (N + x.bn - 1) / x.bn;
+    for (int32_t s : kSlices) {
+      const int64_t units = tiles * s;
+      if (s > 1 && (!may_split || steps < 2 * s || units * x.bm * x.bn * 4 > ws_bytes)) break;
+      if (units > slots && (s > 1 || x.bm < 256)) break;
+      const double full = static_cast<double>(std::min<int64_t>(units, slots)) / slots;
+      const double step = x.step * (x.bm == 256 ? 1.0 + std::max(0.0, full - 0.5) : 1.0 + 0.12 * full);
+      const double waves = static_cast<double>((units + slots - 1) / slots);
+      const double us = x.start + waves * static_cast<double>((steps + s - 1) / s) * step + (s > 1 ? x.red0 + x.red * s : 0.0);
+      if (best.bm == 0 || us < best_us) {
+        best = {x.bm, x.bn, s};
+        best_us = us;
+      }
+    }
+  }
+  return best;
+}
+
 void build_copy_items(const Schedule& s, const std::vector<int32_t>& moved, int64_t row_bytes, int64_t slab,
                       std::vector<CopyItem>* items, std::vector<int32_t>* parts) {
   items->clear();

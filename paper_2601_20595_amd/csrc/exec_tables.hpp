@@ -47,6 +47,19 @@ struct ExecTables {
 // so tiles sharing A rows share an L2; every sub-list keeps the chunk order.
 void build_exec_tables(const Schedule& s, const TileMap& m, const ExecOptions& o, ExecTables* out);
 
+// The tiles a kernel runs a tile map's rows in, and their K-slices.
+struct Geometry {
+  int32_t bm = 0, bn = 0, split = 1;
+};
+
+// Geometry of a bf16 plan that names neither tile shape nor split: 256 x 256 tiles
+// unless they would leave most of the device's `slots` workgroups idle, and then the
+// tile shape and the number of K-slices with the shortest estimated kernel.
+//   group_rows: rows per group (one entry where nothing is grouped)
+//   min_bn: narrowest tiles; may_split: slices may be used; ws_bytes: partial sums they may take
+Geometry choose_geometry(const std::vector<int64_t>& group_rows, int64_t N, int64_t K, int32_t slots, int32_t min_bn,
+                         bool may_split, int64_t ws_bytes);
+
 // Copy items of the kernel copy backend: every chunk of `moved` (chunk ids, in the
 // order the copy workgroups move them) cut into slabs of at most `slab` bytes of
 // rows of `row_bytes`; parts[i] = the items of moved[i].

@@ -182,8 +182,11 @@ struct KernelKey {
   bool reduce = false;  // producer with the all-reduce's fused reduction
 };
 
-// Kernel variants compiled into this library; false if `key` has none.
+// Kernel variants compiled into this library that a plan's configuration may name;
+// false if `key` has none.
 bool kernel_supported(const KernelKey& key);
+// Every variant, those that only the library chooses among them.
+bool kernel_exists(const KernelKey& key);
 // Largest chunk count the per-workgroup ready cache holds.
 int32_t kernel_max_chunks();
 // Persistent grid size: co-resident workgroups on the device.

@@ -9,8 +9,8 @@
 namespace csg {
 
 // Size of the scratch array every device holds (from the library's load until the
-// process ends).
-constexpr size_t kNoAllocScratchBytes = size_t{2} << 20;
+// process ends): 2 MiB of tables and per-call words, 16 MiB of split tiles' partial sums.
+constexpr size_t kNoAllocScratchBytes = size_t{18} << 20;
 
 // Device address of `device`'s copy of the scratch array: looked up once per device
 // (hipGetSymbolAddress with that device current; the caller makes it current) and
