@@ -79,7 +79,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, in
 // another workgroup's abort). A ready value is a load of over a microsecond away, so each
 // lane polls a chunk of its own; polled one after another by one thread, the seven
 // 16-row chunks of a 128-row tile held its unit up for 10 us.
-__device__ int wait_chunks(const GemmArgs& a, int pos, uint32_t* ready_bits, int lane) {
+__device__ __forceinline__ int wait_chunks(const GemmArgs& a, int pos, uint32_t* ready_bits, int lane) {
   int fresh = 0;
   const int p1 = a.list_ptr[pos + 1];
   for (int p0 = a.list_ptr[pos]; p0 < p1; p0 += 64) {
@@ -123,7 +123,7 @@ __device__ int wait_chunks(const GemmArgs& a, int pos, uint32_t* ready_bits, int
 // every chunk has landed, when a wait gave up (the abort flag), or after twice the bound
 // of those waits.
 template <int kThreads>
-__device__ void relay_flags(const GemmArgs& a, int tid) {
+__device__ __forceinline__ void relay_flags(const GemmArgs& a, int tid) {
   static_assert(kMaxChunks / kThreads <= 32, "a thread's chunks fit a mask");
   uint32_t pending = 0;
   for (int i = tid, j = 0; i < a.n_relay; i += kThreads, ++j) pending |= 1u << j;
@@ -143,7 +143,7 @@ __device__ void relay_flags(const GemmArgs& a, int tid) {
 
 // Counts the unit (wave 0, a chunk per lane) against the chunks it read or wrote; the
 // count that completes a chunk sets its flag to the call number.
-__device__ void count_chunks(const GemmArgs& a, int pos, int lane) {
+__device__ __forceinline__ void count_chunks(const GemmArgs& a, int pos, int lane) {
   const int p1 = a.list_ptr[pos + 1];
   for (int p = a.list_ptr[pos] + lane; p < p1; p += 64) {
     const int c = a.list_ids[p];
@@ -157,7 +157,7 @@ __device__ void count_chunks(const GemmArgs& a, int pos, int lane) {
 // GEMM + all-reduce (thread 0 only): waits until the other ranks' partial sums of the
 // own-shard tile's rows have landed (each partial chunk's copy brings its value to
 // 0). 0 when they have, -1 if the wait gave up.
-__device__ int wait_partials(const GemmArgs& a, const TileDesc& td, int pos) {
+__device__ __forceinline__ int wait_partials(const GemmArgs& a, const TileDesc& td, int pos) {
   const int nq = static_cast<int>(a.own_rows / a.own_chunk_rows);
   const int q0 = static_cast<int>((td.row_begin - a.own_row0) / a.own_chunk_rows);
   const int q1 = static_cast<int>((td.row_end - 1 - a.own_row0) / a.own_chunk_rows);
@@ -188,7 +188,7 @@ __device__ int wait_partials(const GemmArgs& a, const TileDesc& td, int pos) {
 // Next execution position for a workgroup on die `xcd` (thread 0 only): the next
 // entry of that die's sub-list, else (when stealing is on) of the following dies'
 // sub-lists; n_tiles when no list it may take from has entries left.
-__device__ int next_tile(const GemmArgs& a, uint32_t xcd) {
+__device__ __forceinline__ int next_tile(const GemmArgs& a, uint32_t xcd) {
   const int dies = a.steal ? kXcdLists : 1;
   for (int d = 0; d < dies; ++d) {
     const int x = static_cast<int>((xcd + d) % kXcdLists);
@@ -391,7 +391,7 @@ struct Bf16Loop {
     issue_rows<B_GROUPS>(rsB, stage + STAGE_A, wave, v_even, v_odd, K, kbase);
   }
 
-  __device__ static void run(unsigned char* lds, const TileGeom& g, f32x16 (&acc)[MI][NI], int wave, int lane) {
+  __device__ __forceinline__ static void run(unsigned char* lds, const TileGeom& g, f32x16 (&acc)[MI][NI], int wave, int lane) {
     const int wm = wave % WAVES_M, wn = wave / WAVES_M;
     const __amdgpu_buffer_rsrc_t rsA = make_rsrc(g.Ab, g.abytes);
     const __amdgpu_buffer_rsrc_t rsB = make_rsrc(g.Bb, g.bbytes);
@@ -543,7 +543,7 @@ struct Bf16PingPong {
   // Compiler memory barrier included: no LDS read or DMA load moves across.
   __device__ __forceinline__ static void barrier() { asm volatile("s_barrier" ::: "memory"); }
 
-  __device__ static void run(unsigned char* lds, const TileGeom& g, f32x16 (&acc)[MI][NI], int wave, int lane) {
+  __device__ __forceinline__ static void run(unsigned char* lds, const TileGeom& g, f32x16 (&acc)[MI][NI], int wave, int lane) {
     const __amdgpu_buffer_rsrc_t rsA = make_rsrc(g.Ab, g.abytes);
     const __amdgpu_buffer_rsrc_t rsB = make_rsrc(g.Bb, g.bbytes);
     const int nk = g.nk;
@@ -688,7 +688,7 @@ struct F32Loop {
   static constexpr int A_PASSES = BM / RPP, B_PASSES = BN / RPP;
   static_assert(BM % RPP == 0 && BN % RPP == 0, "fp32 tile rows");
 
-  __device__ static void run(unsigned char* lds, const TileGeom& g, f32x16 (&acc)[MI][NI], int wave, int lane) {
+  __device__ __forceinline__ static void run(unsigned char* lds, const TileGeom& g, f32x16 (&acc)[MI][NI], int wave, int lane) {
     const int tid = wave * 64 + lane;
     const int wm = wave % WAVES_M, wn = wave / WAVES_M;
     const __amdgpu_buffer_rsrc_t rsA = make_rsrc(g.Ab, g.abytes);
@@ -751,13 +751,23 @@ struct F32Loop {
 constexpr int kDropOffset = 0x7ffffff0;  // buffer offset past every C resource: store dropped
 constexpr int kPolicySc0 = 1, kPolicySc1 = 16;  // cache-policy bits of buffer instructions (scope)
 
+// 16-byte store at byte off of a resource. The scalar offset operand stays 0: the hardware
+// still reads the data registers of a wide store for a few cycles after it has issued, and
+// the compiler keeps a following VALU instruction from overwriting them only when the
+// store has no scalar offset register. With one, the next run's address reached C in
+// place of a result (lanes 12-15 of a row of 16, a call in ten).
+template <int kPolicy>
+__device__ __forceinline__ void store_b128(const u32x4& v, const __amdgpu_buffer_rsrc_t& rs, int off) {
+  __builtin_amdgcn_raw_buffer_store_b128(v, rs, off, 0, kPolicy);
+}
+
 // Split-K partial sums. The slices of a tile may run on different dies, whose L2s are
 // not coherent with each other: every partial is written through to memory and read
 // back past both caches (system-coherent policy, sc0 sc1), so a store that has
 // completed is visible to a reader on any die and no cache is written back or
 // invalidated.
-__device__ __forceinline__ void store_partial(const f32x4& v, const __amdgpu_buffer_rsrc_t& rs, int voff, int soff) {
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rs, voff, soff, kPolicySc0 | kPolicySc1);
+__device__ __forceinline__ void store_partial(const f32x4& v, const __amdgpu_buffer_rsrc_t& rs, int off) {
+  store_b128<kPolicySc0 | kPolicySc1>(__builtin_bit_cast(u32x4, v), rs, off);
 }
 __device__ __forceinline__ f32x4 load_partial(const __amdgpu_buffer_rsrc_t& rs, int voff, int soff) {
   return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff, soff, kPolicySc0 | kPolicySc1));
@@ -814,7 +824,7 @@ __device__ __forceinline__ void add_stored_pair(Load load, Own own, Store store)
 // Waits (thread 0 only) until `others` slices of a split tile have stored their
 // partial sums (high half of the tile's slot word). 1 when they have, -1 if the wait
 // gave up (timeout, or another workgroup's abort).
-__device__ int wait_slices_stored(const GemmArgs& a, const uint32_t* word, int others, int pos) {
+__device__ __forceinline__ int wait_slices_stored(const GemmArgs& a, const uint32_t* word, int others, int pos) {
   const uint64_t t0 = wall_clock64();
   uint32_t v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   while (static_cast<int>(v >> 16) < others) {
@@ -836,7 +846,7 @@ __device__ int wait_slices_stored(const GemmArgs& a, const uint32_t* word, int o
 }
 
 template <int kRuns, class Load, class Store>
-__device__ void reduce_slices(int n, Load load, Store store) {
+__device__ __forceinline__ void reduce_slices(int n, Load load, Store store) {
   switch (n) {
     case 2: reduce_fixed<2, kRuns>(load, store); break;
     case 3: reduce_fixed<3, kRuns>(load, store); break;
@@ -873,7 +883,7 @@ __device__ void reduce_slices(int n, Load load, Store store) {
 // caches on first sight, as with the copy engines). Copy workgroups never wait for
 // tiles, so the chunks always land.
 template <int kThreads>
-__device__ void copy_chunks(const GemmArgs& a, int tid, int copier, int n_copiers) {
+__device__ __forceinline__ void copy_chunks(const GemmArgs& a, int tid, int copier, int n_copiers) {
   constexpr int U = 8;
   constexpr int kStep = kThreads * 16 * U;
   const uint64_t t0 = a.copy_state->t0;
@@ -946,7 +956,7 @@ __device__ void copy_chunks(const GemmArgs& a, int tid, int copier, int n_copier
 // multiple of 4), reread from L2 where the tile's stores just landed, written
 // through to memory. kRowBytes is the widest segment (a full tile row).
 template <int kThreads, int kRowBytes>
-__device__ void send_tile(const __amdgpu_buffer_rsrc_t& rsC, unsigned char* dst, int rows, int row_bytes, int pitch,
+__device__ __forceinline__ void send_tile(const __amdgpu_buffer_rsrc_t& rsC, unsigned char* dst, int rows, int row_bytes, int pitch,
                           int tid) {
   constexpr int kUnitsPerRow = kRowBytes / 8;
   constexpr int U = 8;
@@ -1125,23 +1135,27 @@ __global__ __launch_bounds__(Loop::THREADS, 1) void chunk_gemm(GemmArgs a) {
     // field (j, q), so no per-run offsets stay live across tiles
     const int vrow = Loop::wave_row(wave) + Loop::lane_row(lane);  // row of run (i, q): vrow + run_row(i, q)
     const int vcol = Loop::wave_col(wave) + Loop::lane_col(lane);  // column of run (j, q): vcol + run_col(j, q)
-    const int voff_c = (vrow * N32 + vcol) * kOutBytes;
-    auto store_run = [&](int r, const f32x4& f) {
+    int voff_c = (vrow * N32 + vcol) * kOutBytes;
+    if constexpr (!kOutBf16) asm volatile("" : "+v"(voff_c));  // row offsets added per run, not held across tiles
+    // (inlined whatever its size: a call here would put every accumulator in memory)
+    auto store_run = [&](int r, const f32x4& f) __attribute__((always_inline)) {
       const int i = r / (NI * 4), j = (r / 4) % NI, q = r % 4;
       // N is a multiple of 4: a run is all in or all out
       const bool ok = (vrow + Loop::run_row(i, q) < g.arows) && (vcol + Loop::run_col(j, q) < g.brows);
-      const int voff = (ok ? voff_c : kDropOffset) + Loop::run_col(j, q) * kOutBytes;
       const int soff = __builtin_amdgcn_readfirstlane(Loop::run_row(i, q) * N32 * kOutBytes);
-      if constexpr (kOutBf16)  // v_cvt_pk_bf16_f32: round to nearest even (the default rounding mode)
+      if constexpr (kOutBf16) {  // v_cvt_pk_bf16_f32: round to nearest even (the default rounding mode)
+        const int voff = (ok ? voff_c : kDropOffset) + Loop::run_col(j, q) * kOutBytes;
         __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, __builtin_convertvector(f, bf16x4)), rsC, voff,
                                               soff, kCStorePolicy);
-      else
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, f), rsC, voff, soff, kCStorePolicy);
+      } else {
+        const int voff = (ok ? voff_c + soff : kDropOffset) + Loop::run_col(j, q) * kOutBytes;
+        store_b128<kCStorePolicy>(__builtin_bit_cast(u32x4, f), rsC, voff);
+      }
     };
     // Producer: the previous call's copy out of a chunk reads the same rows of C this
     // unit is about to write; wait until it has completed (its completion signal reads
     // 0). It normally has, long ago. False if the wait gave up.
-    auto wait_previous_copy_out = [&]() -> bool {
+    auto wait_previous_copy_out = [&]() __attribute__((always_inline)) -> bool {
       if constexpr (!kProducer) return true;
       __syncthreads();
       if (wave == 0) {
@@ -1151,7 +1165,7 @@ __global__ __launch_bounds__(Loop::THREADS, 1) void chunk_gemm(GemmArgs a) {
       __syncthreads();
       return __builtin_amdgcn_readfirstlane(s_state) >= 0;
     };
-    auto acc_run = [&](int r) -> f32x4 {
+    auto acc_run = [&](int r) __attribute__((always_inline)) -> f32x4 {
       const int i = r / (NI * 4), j = (r / 4) % NI, q = r % 4;
       return f32x4{acc[i][j][4 * q + 0], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
     };
@@ -1281,7 +1295,8 @@ __global__ __launch_bounds__(Loop::THREADS, 1) void chunk_gemm(GemmArgs a) {
       constexpr int kSliceBytes = kRuns * kThreads * 16;  // one slice of one tile
       const __amdgpu_buffer_rsrc_t rsW = make_rsrc(a.ws + static_cast<int64_t>(td.slot) * (kSliceBytes / 4),
                                                    2 * static_cast<int64_t>(kSliceBytes));
-      const int toff = tid * 16;
+      int toff = tid * 16;
+      asm volatile("" : "+v"(toff));  // the offsets derived from it are computed here, not held across tiles
       const int me = td.slice & 0xffff;
       uint32_t* word = a.slot_count + a.raster[pos];
       if (tid == 0)
@@ -1289,7 +1304,7 @@ __global__ __launch_bounds__(Loop::THREADS, 1) void chunk_gemm(GemmArgs a) {
       __syncthreads();
       if (!__builtin_amdgcn_readfirstlane(s_state)) {
 #pragma unroll
-        for (int r = 0; r < kRuns; ++r) store_partial(acc_run(r), rsW, toff, me * kSliceBytes + r * kThreads * 16);
+        for (int r = 0; r < kRuns; ++r) store_partial(acc_run(r), rsW, toff + me * kSliceBytes + r * kThreads * 16);
         wait_dma_all();  // this thread's partials have been written to memory
         __syncthreads();
         if (tid == 0) __hip_atomic_fetch_add(word, 1u << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1316,10 +1331,11 @@ __global__ __launch_bounds__(Loop::THREADS, 1) void chunk_gemm(GemmArgs a) {
       // through a buffer resource so the per-run offset is a scalar operand
       const __amdgpu_buffer_rsrc_t rsW = make_rsrc(a.ws + static_cast<int64_t>(td.slot) * (kSliceBytes / 4),
                                                    static_cast<int64_t>(nslices) * kSliceBytes);
-      const int toff = tid * 16;
+      int toff = tid * 16;
+      asm volatile("" : "+v"(toff));  // the offsets derived from it are computed here, not held across tiles
       const int mine = (td.slice & 0xffff) * kSliceBytes;
 #pragma unroll
-      for (int r = 0; r < kRuns; ++r) store_partial(acc_run(r), rsW, toff, mine + r * kThreads * 16);
+      for (int r = 0; r < kRuns; ++r) store_partial(acc_run(r), rsW, toff + mine + r * kThreads * 16);
       // waiting for the stores to complete (written through to memory) is the release;
       // the reducer reads memory past its caches
       wait_dma_all();
@@ -1379,12 +1395,12 @@ __global__ __launch_bounds__(Loop::THREADS, 1) void chunk_gemm(GemmArgs a) {
             const int row0 = wave * kRowsPerWave + 2 * q2;  // this instruction's rows: row0 + pr
             const u32x4 v =
                 *reinterpret_cast<const u32x4*>(lds + (row0 + pr) * kRowB + ((pc ^ ((row0 + pr) & 31)) << 4));
-            const int voff = row0 + pr < g.arows ? vlane : kDropOffset;
             const int soff = __builtin_amdgcn_readfirstlane(row0 * N32 * 2);
+            const int voff = row0 + pr < g.arows ? vlane + soff : kDropOffset;
             if (c8 + 8 <= g.brows)
-              __builtin_amdgcn_raw_buffer_store_b128(v, rsC, voff, soff, kCStorePolicy);
+              store_b128<kCStorePolicy>(v, rsC, voff);
             else if (c8 + 4 <= g.brows)  // N is a multiple of 4: a half piece ends the row
-              __builtin_amdgcn_raw_buffer_store_b64(u32x2{v.x, v.y}, rsC, voff, soff, kCStorePolicy);
+              __builtin_amdgcn_raw_buffer_store_b64(u32x2{v.x, v.y}, rsC, voff, 0, kCStorePolicy);
           }
         }
       } else if (!skip) {

@@ -39,3 +39,28 @@ def test_pipeline_edges_bit_exact(tile, steps, split, op):
         R, _, _ = oracle.gemm_rs(d.A.device_array, d.B.device_array, chunks, order)
     assert np.array_equal(out_to_f64(c, "bf16"), bf16_rne_of_f64(R))
     plan.close()
+
+
+@pytest.mark.parametrize("split", [2, 3])
+def test_wide_stores_of_split_tiles_hold_on_every_call(split):
+    """fp32 output and partial sums leave as 16-byte stores, whose registers the next run's
+    arithmetic reuses: forty calls, each bit for bit (a lost register showed in one call of
+    ten)."""
+    W, S, N, K = 2, 1280, 648, 512
+    print("wide stores", split, flush=True)
+    g = torch.Generator(device="cuda:0").manual_seed(5)
+    a = torch.randint(-2, 3, (W * S, K), generator=g, device="cuda:0").to(torch.bfloat16)
+    b = torch.randint(-2, 3, (N, K), generator=g, device="cuda:0").to(torch.bfloat16)
+    want = a.float() @ b.float().t()               # exact: every sum is below 2^24
+    plan = csg.Plan("ag", W * S, N, K, "bf16", "f32", csg.Schedule.uniform(W, 0, S, 5, "ring"),
+                    cfg={"split_k": split, "timeout_ms": 1000})
+    st, cp = torch.cuda.Stream(), torch.cuda.Stream()
+    land, c = a.clone(), torch.empty_like(want)
+    for i in range(40):
+        c.fill_(float("nan"))
+        torch.cuda.synchronize()
+        plan.ag_gemm(land, a, b, c, "overlap", st, cp)
+        plan.check()
+        torch.cuda.synchronize()
+        assert torch.equal(c, want), i
+    plan.close()

@@ -143,3 +143,15 @@ def test_library_kernels_have_no_per_lane_barrier_loop(source):
     kernels = re.findall(r"^(_Z\S+):", asm, re.M)
     assert kernels, "no kernels found in %s" % source
     assert divergent_barrier_loops(asm) == []
+
+
+@pytest.mark.parametrize("source", KERNEL_SOURCES)
+def test_no_wide_store_with_a_scalar_offset_register(source):
+    """A buffer store of 12 or 16 bytes per lane reads its data registers for a few cycles
+    after it has issued. The compiler protects them from the next VALU write only when the
+    store's scalar offset is no register; with one, results were replaced by the next
+    address now and then. Every such store must therefore have none."""
+    asm = device_asm(os.path.join(ROOT, "paper_2601_20595_amd", "csrc", source))
+    wide = re.findall(r"^\s*(buffer_store_dwordx[34] .*)$", asm, re.M)
+    assert source != "chunk_gemm.hip" or wide
+    assert [w for w in wide if re.search(r"\], s\d+ ", w)] == []
