@@ -122,9 +122,10 @@ typedef struct {
  *                   cut into bands of group_m and each band is visited column by column:
  *                   order = (key, band, n, m)
  *   group_m         band height of intra_order 1 (0 = 8)
- *   tile_dispatch   0 or 1 = workgroups take the next entry of the tile list from an
- *                   atomic ticket (with num_workgroups 0, a list no longer than the
- *                   co-resident slots is dealt statically, one entry per workgroup, in an
+ *   tile_dispatch   1 = workgroups take the next entry of the tile list from an atomic
+ *                   ticket; 0 = the same for plans with split tiles, num_workgroups or kernel
+ *                   copies, else static as for 2 (with num_workgroups 0, 0 and 1 deal a list
+ *                   no longer than the co-resident slots one entry per workgroup, in an
  *                   order chosen for the caches); 2 = static: workgroup w takes entries s, s + G, s + 2G,
  *                   ... with s = (w mod 8) * (G / 8) + w / 8 when G is a multiple of 8
  *                   (else s = w), so that the workgroups of one die (the dispatcher

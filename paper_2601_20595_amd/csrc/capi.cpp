@@ -137,6 +137,7 @@ struct csg_plan {
   int32_t ws_slices = 0;               // partial-sum buffers of split tiles (0: nothing is split)
   int32_t tail_begin = 0;              // static dispatch: first unit dealt from the shared ticket
   bool one_shot = false;               // every unit has a workgroup of its own (static slots)
+  bool static_units = false;           // units are dealt statically (one-shot, named or chosen)
   int32_t unit_wg0 = 0;                // one-shot: workgroups that only copy or relay, before those of the units
   // One-shot consumers with slots to spare: workgroup 0 relays the copies' completion
   // values into words in device memory. n_relay chunks (remote_order), words by call parity.
@@ -369,6 +370,17 @@ csg_status setup_device(csg_plan* p) {
   if (p->cfg.num_workgroups == 0) eo.slots = p->grid - copiers;
   csg::ExecTables et;
   csg::build_exec_tables(p->sched, m, eo, &et);
+  // Several waves of whole tiles, copied by the engines: dealt statically, die by die, unless
+  // tickets are named. The tiles take equal times, so tickets balance nothing, and taking
+  // one costs about a microsecond per tile: gemm-rs 8192 x 4096 x 1792 122 -> 115 us, grouped
+  // 32768 x 1792 x 4096 459 -> 453, all-gather 16384 x 3584 x 8192 778 -> 765. Copy workgroups
+  // keep tickets: they join late.
+  if (!et.one_shot && p->cfg.tile_dispatch == 0 && p->cfg.num_workgroups == 0 && !p->kernel_copies() &&
+      et.ws_slices == 0) {
+    eo.tile_dispatch = 2;
+    csg::build_exec_tables(p->sched, m, eo, &et);
+  }
+  p->static_units = et.one_shot || eo.tile_dispatch == 2;
   if (et.one_shot) {
     p->one_shot = true;
     p->unit_wg0 = copiers;
@@ -739,7 +751,7 @@ csg_status launch_gemm(csg_plan* p, const void* A, const void* B, void* C, csg_m
     a.ready = p->d_ready_relay[set];
   }
   a.n_chunks = p->n_chunks();
-  a.dynamic_ticket = p->cfg.tile_dispatch == 2 || p->one_shot ? 0 : 1;
+  a.dynamic_ticket = p->static_units ? 0 : 1;
   a.tail_begin = p->tail_begin;
   a.unit_wg0 = p->unit_wg0;
   // Idle workgroups take other dies' units (split tiles exchange partial sums through
