@@ -111,11 +111,11 @@ typedef struct {
  *                   (bk = 64 for bf16, 16 for fp32): bf16 inputs 256 x 256 (every operation;
  *                   the default), 256 x 224 (all-gather and grouped GEMMs), 128 x 256
  *                   (those and GEMM + reduce-scatter, bf16 output), 256 x 128 and 128 x 128
- *                   (all-gather and grouped GEMMs, bf16 output); fp32 inputs 64 x 64. A bf16
+ *                   (all-gather and grouped GEMMs, bf16 output); fp32 inputs 64 x 64. A
  *                   plan that names neither bm nor bn, tail split, tail_wave nor
- *                   num_workgroups keeps 256 x 256 as its tile (the map, the tile list, the
+ *                   num_workgroups keeps 256 x 256 (fp32 64 x 64) as its tile (the map, the tile list, the
  *                   ids in traces and diagnostics), and where such tiles would leave most
- *                   CUs idle its kernel runs each tile as several smaller ones
+ *                   CUs idle its kernel runs each tile as several smaller ones or K-slices
  *   intra_order     tile order inside a chunk (Section 5.2, intra-chunk swizzle), the
  *                   chunk order staying as it is: 0 = raster (m, n), the local kernel's
  *                   own traversal; 1 = the row tiles sharing a chunk key, ascending, are
@@ -368,8 +368,8 @@ csg_status csg_ag_gemm(csg_plan* p, void* a_landing, const void* a_staging, cons
  * covers exactly M rows; a_landing (M x K, local rows in place), a_staging (same
  * layout, the remote rows), b_nk (N x K), c (M x N) are device buffers of `device`,
  * 16-byte aligned; tiles are 256 x 256 x 64 (bf16 input; smaller ones and K-slices where
- * those would leave CUs idle, as for a plan) or 64 x 64 x 16 (f32), dispatched per die with
- * stealing. copy_workgroups: workgroups that move the chunks
+ * those would leave CUs idle, as for a plan) or 64 x 64 x 16 (f32, also in K-slices),
+ * dispatched per die with stealing. copy_workgroups: workgroups that move the chunks
  * (0 = 16). Modes as for csg_ag_gemm (compute-only: a_landing already holds every row;
  * copy-only: the copy workgroups alone run).
  * Limits: at most 4096 chunks, 16384 tiles, 32768 (tile, remote chunk) pairs and 16384

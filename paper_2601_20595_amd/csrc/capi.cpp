@@ -1477,13 +1477,15 @@ csg_status csg_plan_create(csg_op op, int64_t M, int64_t N, int64_t K, csg_dtype
       p->kbm = c.bm;
       p->kbn = c.bn;
       p->ksplit = c.split_k;
-      const bool free_tiles = bf16 && !named_tiles && c.tail_split <= 1 && c.tail_wave <= 1 &&
+      const bool free_tiles = !named_tiles && c.tail_split <= 1 && c.tail_wave <= 1 &&
                               c.split_k <= 1 && c.num_workgroups == 0;
+      int cus = 0;
+      if (e == hipSuccess && free_tiles) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
       if (e == hipSuccess && free_tiles) {
         const int32_t copiers = p->kernel_copies() && p->consumer() ? copier_slots(c.copy_workgroups) : 0;
         const csg::Geometry geo =
-            csg::choose_geometry(groups.empty() ? std::vector<int64_t>{M} : groups, N, K, p->grid - copiers,
-                                 p->allreduce() ? 128 : 64, free_split && !p->allreduce(), int64_t{1} << 30);
+            csg::choose_geometry(bf16, groups.empty() ? std::vector<int64_t>{M} : groups, N, K, cus - copiers,
+                                 bf16 && p->allreduce() ? 128 : 64, free_split && !p->allreduce(), int64_t{1} << 30);
         csg::KernelKey key = p->key;
         key.bm = geo.bm;
         key.bn = geo.bn;
@@ -1675,9 +1677,11 @@ csg_status csg_ag_gemm_noalloc(const csg_schedule* sched, int64_t M, int64_t N, 
   hipStream_t stream = static_cast<hipStream_t>(stream_v);
   if (nd.sig != sig) {
     int32_t grid = nd.grid[kslot];
-    if (bf16) {
+    {
       // smaller tiles and K-slices for launches that leave CUs idle, where they fit the scratch
-      const csg::Geometry geo = csg::choose_geometry({M}, N, K, grid - copiers, 64, true, kNaWorkspace);
+      int cus = 0;
+      CSG_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
+      const csg::Geometry geo = csg::choose_geometry(bf16, {M}, N, K, cus - copiers, 64, true, kNaWorkspace);
       csg::KernelKey k2 = key;
       k2.bm = geo.bm;
       k2.bn = geo.bn;

@@ -24,8 +24,8 @@
 //         LDS rows are 128 bytes with an XOR swizzle of their 16-byte
 //         vectors that keeps both the DMA writes and the ds_read_b128 fragment reads
 //         free of bank conflicts.
-//   fp32: 256 threads = 2 x 2 waves; v_mfma_f32_32x32x2_f32 with register-staged,
-//         padded LDS tiles.
+//   fp32: 256 threads = 2 x 2 waves; v_mfma_f32_32x32x2_f32, tiles by the same DMA and
+//         swizzle in a three-stage ring.
 // The MFMA takes the B fragment as its first operand, so each lane ends up with runs
 // of four consecutive output columns of one output row (the loop's lane_row,
 // lane_col, run_row and run_col say where), which the epilogue writes as 8-byte
@@ -665,9 +665,18 @@ struct Bf16PingPong {
 
 
 // ---------------------------------------------------------------------------------
-// fp32 main loop: register-staged, padded LDS rows, BK = 16
+// fp32 main loop: LDS DMA, XOR-swizzled 128-byte rows, stages of 32 k in steps of 16
 // ---------------------------------------------------------------------------------
-template <int BM_, int BN_>
+// v_mfma_f32_32x32x2_f32 takes one k per half wave. A lane's 16-byte fragment holds four
+// consecutive k of its row, lanes 0-31 the even and lanes 32-63 the odd 16-byte vectors, so
+// one LDS read per operand feeds four MFMAs (256 cycles); the k pairs (e, e + 4) are summed
+// together, in both operands alike. Bound: the matrix cores (64 cycles per MFMA). The
+// register-staged loop before it read 4 bytes per lane and MFMA and waited for its global
+// loads at every 16 k: 4096 x 4096 x 2048 697 -> 607 us (99 -> 113 TFLOP/s), 2048 x 1024 x 1024
+// 54 -> 47 (as gemm-rs 75 -> 64), 256 x 256 x 256 14.6 -> 12.4. K is a multiple of 16: in a
+// last half stage the missing vectors take an offset past the resource's end and read as
+// zeros.
+template <int BM_, int BN_, int STAGES>
 struct F32Loop {
   // output layout: as the bf16 loop's 32 x 32 x 16 one (row lane % 32, runs of four
   // columns at 4 (lane / 32) + 8 q)
@@ -679,66 +688,87 @@ struct F32Loop {
   static constexpr int run_row(int i, int) { return 32 * i; }
   static constexpr int run_col(int j, int q) { return 32 * j + 8 * q; }
   static constexpr int BM = BM_, BN = BN_, BK = 16, IN_BYTES = 4;
-  static constexpr int WAVES_M = 2, WAVES_N = 2, THREADS = 256;
+  static constexpr int WAVES_M = 2, WAVES_N = 2, WAVES = 4, THREADS = 256;
   static constexpr int WTM = BM / 2, WTN = BN / 2, MI = WTM / 32, NI = WTN / 32;
-  static constexpr int LDK = BK + 4;                      // floats per LDS row
-  static constexpr int STAGE_A = BM * LDK * 4, STAGE_B = BN * LDK * 4;
-  static constexpr int LDS_BYTES = 2 * (STAGE_A + STAGE_B);
-  static constexpr int RPP = THREADS / (BK / 4);          // rows per load pass
-  static constexpr int A_PASSES = BM / RPP, B_PASSES = BN / RPP;
-  static_assert(BM % RPP == 0 && BN % RPP == 0, "fp32 tile rows");
+  static constexpr int ROWB = 128;  // bytes per LDS row (32 floats)
+  static constexpr int STAGE_A = BM * ROWB, STAGE = (BM + BN) * ROWB;
+  static constexpr int LDS_BYTES = STAGES * STAGE;
+  static constexpr int A_LOADS = BM / 8 / WAVES, B_LOADS = BN / 8 / WAVES, LOADS = A_LOADS + B_LOADS;
+  static_assert(A_LOADS % 2 == 0 && B_LOADS % 2 == 0 && STAGES >= 3, "fp32 tile shape");
+
+  // LDS swizzle as Bf16Loop's
+  __device__ static int swz(int r) { return (r & 7) ^ ((r >> 3) & 1); }
 
   __device__ __forceinline__ static void run(unsigned char* lds, const TileGeom& g, f32x16 (&acc)[MI][NI], int wave, int lane) {
-    const int tid = wave * 64 + lane;
-    const int wm = wave % WAVES_M, wn = wave / WAVES_M;
     const __amdgpu_buffer_rsrc_t rsA = make_rsrc(g.Ab, g.abytes);
     const __amdgpu_buffer_rsrc_t rsB = make_rsrc(g.Bb, g.bbytes);
-    const int nk = g.nk;
-    const int vrow = tid / (BK / 4), vcol = (tid % (BK / 4)) * 4;
-    const int voff = (vrow * static_cast<int>(g.K) + vcol) * 4;
-    const int pass_bytes = RPP * static_cast<int>(g.K) * 4;
-    u32x4 ra[A_PASSES], rb[B_PASSES];
-    auto load = [&](int kt) {
+    const int stages = (g.nk + 1) / 2;
+    const uint32_t lds_base =
+        __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_ptr_t)lds)));
+    const uint32_t row_b = static_cast<uint32_t>(g.K) * 4;
+    const int lr = lane >> 3;
+    const int vec_even = (lane & 7) ^ lr, vec_odd = vec_even ^ 1;  // logical vector this lane fetches, by row parity
+    const uint32_t va = (wave * A_LOADS * 8 + lr) * row_b, vb = (wave * B_LOADS * 8 + lr) * row_b;
+    const uint32_t la = __builtin_amdgcn_readfirstlane(lds_base + wave * A_LOADS * 1024);
+    const uint32_t lb = __builtin_amdgcn_readfirstlane(lds_base + STAGE_A + wave * B_LOADS * 1024);
+    constexpr uint32_t kPast = 0x7ffffff0u;  // past every resource, and no wrap when an offset is added
+    // stage t into ring slot `slot`; past the last stage every load falls past its resource
+    auto issue = [&](int t, int slot) __attribute__((always_inline)) {
+      const uint32_t kb = t < stages ? static_cast<uint32_t>(t) * 128u : kPast;
+      const bool half = 2 * t + 2 > g.nk;
+      auto load = [&](const __amdgpu_buffer_rsrc_t& rs, uint32_t l0, uint32_t row0, int q) __attribute__((always_inline)) {
+        const int vec = (q & 1) ? vec_odd : vec_even;
+        const uint32_t v = (half && vec >= 4) ? (t < stages ? kPast : 0u) : row0 + vec * 16;
+        dma16(rs, l0 + q * 1024, v, kb + q * 8 * row_b);
+      };
 #pragma unroll
-      for (int p = 0; p < A_PASSES; ++p)
-        ra[p] = __builtin_amdgcn_raw_buffer_load_b128(rsA, voff + kt * BK * 4 + p * pass_bytes, 0, 0);
+      for (int q = 0; q < A_LOADS; ++q) load(rsA, la + slot * STAGE, va, q);
 #pragma unroll
-      for (int p = 0; p < B_PASSES; ++p)
-        rb[p] = __builtin_amdgcn_raw_buffer_load_b128(rsB, voff + kt * BK * 4 + p * pass_bytes, 0, 0);
+      for (int q = 0; q < B_LOADS; ++q) load(rsB, lb + slot * STAGE, vb, q);
     };
-    auto store = [&](int buf) {
-      float* sa = reinterpret_cast<float*>(lds + buf * (STAGE_A + STAGE_B));
-      float* sb = reinterpret_cast<float*>(lds + buf * (STAGE_A + STAGE_B) + STAGE_A);
+    const int lrow = lane & 31, lk = lane >> 5, sw = swz(lrow);
+    const int a_off = (wave_row(wave) + lrow) * ROWB;
+    const int b_off = STAGE_A + (wave_col(wave) + lrow) * ROWB;
+    f32x4 fa[2][MI], fb[2][NI];  // fragments of two consecutive k sub-steps (8 k each)
+    auto load_frags = [&](int set, int slot, int ks) __attribute__((always_inline)) {
+      const unsigned char* st = lds + slot * STAGE;
+      const int vec = ((2 * ks + lk) ^ sw) * 16;
 #pragma unroll
-      for (int p = 0; p < A_PASSES; ++p) *reinterpret_cast<u32x4*>(sa + (vrow + p * RPP) * LDK + vcol) = ra[p];
+      for (int i = 0; i < MI; ++i) fa[set][i] = *reinterpret_cast<const f32x4*>(st + a_off + i * 32 * ROWB + vec);
 #pragma unroll
-      for (int p = 0; p < B_PASSES; ++p) *reinterpret_cast<u32x4*>(sb + (vrow + p * RPP) * LDK + vcol) = rb[p];
+      for (int j = 0; j < NI; ++j) fb[set][j] = *reinterpret_cast<const f32x4*>(st + b_off + j * 32 * ROWB + vec);
     };
-    const int lrow = lane & 31, lhalf = lane >> 5;
-    load(0);
-    store(0);
+#pragma unroll
+    for (int s = 0; s < STAGES - 1; ++s) issue(s, s);
+    wait_dma_keep<(STAGES - 2) * LOADS>();
     __syncthreads();
-    for (int t = 0; t < nk; ++t) {
-      const int buf = t & 1;
-      if (t + 1 < nk) load(t + 1);
-      const float* sa = reinterpret_cast<const float*>(lds + buf * (STAGE_A + STAGE_B));
-      const float* sb = reinterpret_cast<const float*>(lds + buf * (STAGE_A + STAGE_B) + STAGE_A);
+    load_frags(0, 0, 0);
+    int slot = 0;
+    for (int t = 0; t < stages; ++t) {
+      const int next = slot + 1 == STAGES ? 0 : slot + 1;
+      issue(t + STAGES - 1, slot == 0 ? STAGES - 1 : slot - 1);  // the slot of stage t - 1, read by all
 #pragma unroll
-      for (int ks = 0; ks < BK; ks += 2) {
-        float af[MI], bfr[NI];
+      for (int ks = 0; ks < 4; ++ks) {
+        const int cur = ks & 1;
+        if (ks < 3) {
+          load_frags(cur ^ 1, slot, ks + 1);
+        } else {
+          wait_dma_keep<(STAGES - 2) * LOADS>();  // stage t + 1 has landed
+          __syncthreads();
+          load_frags(cur ^ 1, next, 0);  // (after the last stage: zeros or old values, not used)
+        }
 #pragma unroll
-        for (int i = 0; i < MI; ++i) af[i] = sa[(wm * WTM + i * 32 + lrow) * LDK + ks + lhalf];
+        for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int j = 0; j < NI; ++j) bfr[j] = sb[(wn * WTN + j * 32 + lrow) * LDK + ks + lhalf];
+          for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-          for (int j = 0; j < NI; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(bfr[j], af[i], acc[i][j], 0, 0, 0);
+            for (int j = 0; j < NI; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fb[cur][j][e], fa[cur][i][e], acc[i][j], 0, 0, 0);
       }
-      if (t + 1 < nk) store(buf ^ 1);
-      __syncthreads();
+      slot = next;
     }
+    wait_dma_all();  // the loads past the last stage
+    __syncthreads();
   }
 };
 
@@ -1487,7 +1517,7 @@ using LoopBf16_128x256 = Bf16Loop<128, 256, 2, 4, 3, 16>;
 using LoopBf16_128 = Bf16Loop<128, 128, 2, 4, 3, 16>;
 using LoopBf16_128x64 = Bf16Loop<128, 64, 4, 2, 3, 16>;
 using LoopBf16_256x224 = Bf16Loop<256, 224, 8, 1>;
-using LoopF32_64 = F32Loop<64, 64>;
+using LoopF32_64 = F32Loop<64, 64, 3>;
 
 // The timing events (either may be null) take the dispatch's own start and end
 // timestamps, not those of separate markers queued around it.

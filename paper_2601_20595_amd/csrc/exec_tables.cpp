@@ -169,27 +169,28 @@ void build_exec_tables(const Schedule& s, const TileMap& m, const ExecOptions& o
 //                       tiles, two waves)
 // 256 x 256 tiles run whole wave after whole wave; the small ones, whose operands cost
 // twice the traffic per product, only where all of them run at once.
-Geometry choose_geometry(const std::vector<int64_t>& group_rows, int64_t N, int64_t K, int32_t slots, int32_t min_bn,
-                         bool may_split, int64_t ws_bytes) {
+Geometry choose_geometry(bool bf16, const std::vector<int64_t>& group_rows, int64_t N, int64_t K, int32_t slots,
+                         int32_t min_bn, bool may_split, int64_t ws_bytes) {
   struct Tile {
+    bool bf16;
     int32_t bm, bn;
     double start, step, red0, red;
   };
-  static const Tile kTiles[] = {{256, 256, 10.0, 1.08, 3.0, 4.0}, {128, 128, 8.0, 0.46, 2.0, 1.0},
-                                {128, 64, 6.5, 0.34, 1.0, 0.9}};
+  static const Tile kTiles[] = {{true, 256, 256, 10.0, 1.08, 3.0, 4.0}, {true, 128, 128, 8.0, 0.46, 2.0, 1.0},
+                                {true, 128, 64, 6.5, 0.34, 1.0, 0.9}, {false, 64, 64, 6.0, 0.23, 1.0, 0.5}};
   static const int32_t kSlices[] = {1, 2, 3, 4, 6, 8};
-  const int64_t steps = K / 64;
+  const int64_t steps = K / (bf16 ? 64 : 16);
   Geometry best;
   double best_us = 0.0;
   for (const Tile& x : kTiles) {
-    if (x.bn < min_bn) continue;
+    if (x.bf16 != bf16 || x.bn < min_bn) continue;
     int64_t tiles = 0;
     for (int64_t rows : group_rows) tiles += (rows + x.bm - 1) / x.bm;
     tiles *= (N + x.bn - 1) / x.bn;
     for (int32_t s : kSlices) {
       const int64_t units = tiles * s;
       if (s > 1 && (!may_split || steps < 2 * s || units * x.bm * x.bn * 4 > ws_bytes)) break;
-      if (units > slots && (s > 1 || x.bm < 256)) break;
+      if (units > slots && (s > 1 || (bf16 && x.bm < 256))) break;
       const double full = static_cast<double>(std::min<int64_t>(units, slots)) / slots;
       const double step = x.step * (x.bm == 256 ? 1.0 + std::max(0.0, full - 0.5) : 1.0 + 0.12 * full);
       const double waves = static_cast<double>((units + slots - 1) / slots);

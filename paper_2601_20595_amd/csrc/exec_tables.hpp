@@ -52,13 +52,14 @@ struct Geometry {
   int32_t bm = 0, bn = 0, split = 1;
 };
 
-// Geometry of a bf16 plan that names neither tile shape nor split: 256 x 256 tiles
-// unless they would leave most of the device's `slots` workgroups idle, and then the
-// tile shape and the number of K-slices with the shortest estimated kernel.
+// Geometry of a plan that names neither tile shape nor split: bf16, 256 x 256 tiles
+// unless they would leave most of the device's `slots` workgroups (one per CU) idle, and
+// then the tile shape and the number of K-slices with the shortest estimated kernel; fp32,
+// 64 x 64 tiles, in K-slices where they would.
 //   group_rows: rows per group (one entry where nothing is grouped)
 //   min_bn: narrowest tiles; may_split: slices may be used; ws_bytes: partial sums they may take
-Geometry choose_geometry(const std::vector<int64_t>& group_rows, int64_t N, int64_t K, int32_t slots, int32_t min_bn,
-                         bool may_split, int64_t ws_bytes);
+Geometry choose_geometry(bool bf16, const std::vector<int64_t>& group_rows, int64_t N, int64_t K, int32_t slots,
+                         int32_t min_bn, bool may_split, int64_t ws_bytes);
 
 // Copy items of the kernel copy backend: every chunk of `moved` (chunk ids, in the
 // order the copy workgroups move them) cut into slabs of at most `slab` bytes of

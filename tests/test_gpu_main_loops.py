@@ -41,6 +41,29 @@ def test_pipeline_edges_bit_exact(tile, steps, split, op):
     plan.close()
 
 
+@pytest.mark.parametrize("steps,split", [(1, 1), (2, 1), (3, 1), (5, 1), (8, 1), (9, 1), (5, 3), (7, 2), (12, 5)])
+@pytest.mark.parametrize("op", ["ag", "rs"])
+def test_fp32_pipeline_edges_bit_exact(steps, split, op):
+    """The fp32 loop's stages hold two K steps of 16: whole and half last stages, slices that
+    begin and end inside a stage, fewer stages than the ring."""
+    W, r, S, N, K = 2, 1, 65, 64 + 4, 16 * steps
+    print("fp32 loop", steps, split, op, flush=True)
+    w = si.Workload(133, "loop", op, M=W * S, N=N, K=K, dtype="f32", out_dtype="f32", dist="int", world=W, rank=r,
+                    shard_rows=S, chunks_per_shard=1, order="ring" if op == "ag" else "rs_ring")
+    d = si.draw(w)
+    chunks, order = oracle.uniform_schedule(W, r, S, 1, w.order)
+    plan = csg.Plan(op, W * S, N, K, "f32", "f32", csg.Schedule.uniform(W, r, S, 1, w.order),
+                    cfg={"timeout_ms": 1000, "split_k": split})
+    if op == "ag":
+        c, _ = run_ag(plan, chunks, d.A, d.B, "f32", repeats=2)
+        R = oracle.ag_gemm(d.A.device_array, d.B.device_array, chunks, order)
+    else:
+        c, _ = run_rs(plan, d.A, d.B, "f32", repeats=2)
+        R, _, _ = oracle.gemm_rs(d.A.device_array, d.B.device_array, chunks, order)
+    assert np.array_equal(out_to_f64(c, "f32"), R)
+    plan.close()
+
+
 @pytest.mark.parametrize("split", [2, 3])
 def test_wide_stores_of_split_tiles_hold_on_every_call(split):
     """fp32 output and partial sums leave as 16-byte stores, whose registers the next run's
