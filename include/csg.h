@@ -463,8 +463,8 @@ csg_status csg_attn_plan_create(int32_t n_heads, int32_t n_kv_heads, int32_t hea
  * one completion signal as the chunk's ready flag) once the previous call's kernel
  * has finished reading those rows, and returns when the copies have completed
  * (copy-only mode: once they are issued, as for csg_ag_gemm). Each
- * work unit (one head, 128 query rows) consumes the chunks in arrival order, waiting
- * for each once. Compute-only: the landing buffers must already hold every row. */
+ * work unit (one head, 128 query rows; where those would leave slots idle, a slice of the
+ * keys of one) consumes the chunks in arrival order, waiting for each once. Compute-only: the landing buffers must already hold every row. */
 csg_status csg_ring_attn(csg_plan* p, const void* q, void* k_landing, void* v_landing,
                          const void* k_staging, const void* v_staging, void* o, void* lse,
                          csg_mode mode, void* compute_stream, void* copy_stream);

@@ -196,6 +196,7 @@ struct csg_plan {
   int32_t ar_chunk_rows = 0, ar_peers = 0, ar_own_shard = 0;
   // ring attention: heads, key/value heads, query rows; device arrays
   int32_t at_heads = 0, at_kv_heads = 0, at_q_rows = 0;
+  int32_t at_slices = 1;               // key slices per (query block, head)
   int32_t* d_arrival = nullptr;        // [n_chunks] chunk id at each arrival position
   int32_t* d_chunk_rows = nullptr;     // [2 * n_chunks] key row begin / end by chunk id
   const void* ar_partials = nullptr;  // this call's partials landing buffer
@@ -233,7 +234,11 @@ struct csg_plan {
   uint32_t* ticket(int set) const { return d_ticket + set * csg::kXcdLists; }
   csg::DeviceDiag* diag(int set) const { return d_diag + set; }
   int64_t* relay(int set) const { return d_relay ? d_relay + static_cast<size_t>(set) * n_relay : nullptr; }
-  uint32_t* slot_count(int set) const { return d_slot_count ? d_slot_count + set * kmap.n_tiles() : nullptr; }
+  // words per set of slot_count: tiles, or attention's (query block, head) pairs
+  int32_t n_slot_words() const { return attention() ? n_units / at_slices : kmap.n_tiles(); }
+  uint32_t* slot_count(int set) const {
+    return d_slot_count ? d_slot_count + static_cast<size_t>(set) * n_slot_words() : nullptr;
+  }
   bool consumer() const { return op == CSG_AG_GEMM || op == CSG_GROUPED_GEMM || attention(); }
   bool attention() const { return attn; }
   // ring attention: copies per chunk (keys and values), both completing its signal
@@ -644,7 +649,7 @@ csg_status launch_prologue_call(csg_plan* p, csg_mode mode, hipStream_t compute)
   pa.ticket = p->ticket(set);
   pa.diag = p->diag(set);
   pa.slot_count = p->slot_count(set);
-  pa.n_slots = p->ws_slices > 0 ? p->kmap.n_tiles() : 0;
+  pa.n_slots = p->d_slot_count ? p->n_slot_words() : 0;
   pa.relay = p->relay(set);
   pa.n_relay = p->n_relay;
   if (p->kernel_copies()) {
@@ -971,7 +976,12 @@ struct CopyIssuer {
 csg_status setup_attn_device(csg_plan* p) {
   DeviceGuard g(p->device);
   if (g.err != hipSuccess) return hip_fail(g.err, "hipSetDevice");
-  p->n_units = ((p->at_q_rows + csg::kAttnBlockQ - 1) / csg::kAttnBlockQ) * p->at_heads;
+  const int64_t whole = static_cast<int64_t>((p->at_q_rows + csg::kAttnBlockQ - 1) / csg::kAttnBlockQ) * p->at_heads;
+  p->at_slices = p->cfg.num_workgroups == 0
+                     ? csg::attn_slices(whole, static_cast<int32_t>(p->sched.total_rows / csg::kAttnBlockKV), p->grid)
+                     : 1;
+  p->n_units = static_cast<int32_t>(whole * p->at_slices);
+  if (p->cfg.num_workgroups == 0) p->grid = std::min(p->grid, round_up_dies(p->n_units));
   std::vector<int32_t> rows(2 * static_cast<size_t>(p->n_chunks()));
   for (int32_t c = 0; c < p->n_chunks(); ++c) {
     rows[2 * c] = static_cast<int32_t>(p->sched.chunks[c].row_begin);
@@ -988,6 +998,10 @@ csg_status setup_attn_device(csg_plan* p) {
   state.add_zeros(&p->d_diag, 2 * sizeof(csg::DeviceDiag));
   state.add_zeros(&p->d_scratch, 64);
   state.add_zeros(&p->d_join_flag, 4);
+  if (p->at_slices > 1) {
+    state.add_zeros(&p->d_slot_count, 2 * static_cast<size_t>(whole) * 4);
+    CSG_HIP(hipMalloc(&p->d_ws, static_cast<size_t>(p->n_units) * csg::kAttnPartBytes));
+  }
   if ((st = state.commit(&p->d_state)) != CSG_OK) return st;
   CSG_HIP(hipHostMalloc(&p->h_out_flags, nflag * 4, hipHostMallocMapped | hipHostMallocCoherent));
   std::memset(p->h_out_flags, 0, nflag * 4);
@@ -1034,6 +1048,14 @@ csg_status launch_attn(csg_plan* p, const void* q, const void* k, const void* v,
   a.H = p->at_heads;
   a.Hkv = p->at_kv_heads;
   a.n_units = p->n_units;
+  a.slices = p->at_slices;
+  a.n_blocks = static_cast<int32_t>(p->sched.total_rows / csg::kAttnBlockKV);
+  const size_t whole = static_cast<size_t>(p->n_units / p->at_slices);
+  if (p->at_slices > 1) {
+    a.ws = p->d_ws;
+    a.slot_count = p->d_slot_count + static_cast<size_t>(set) * whole;
+    a.next_slot_count = p->d_slot_count + static_cast<size_t>(next) * whole;
+  }
   a.n_chunks = p->n_chunks();
   a.arrival = p->d_arrival;
   a.chunk_rows = p->d_chunk_rows;

@@ -8,7 +8,10 @@
 // chunk's ready flag (at most once per chunk and workgroup), then runs the
 // flash-attention recurrence over the chunk's keys in blocks of 64. After its last
 // block of a chunk it counts the chunk, and the unit that completes the count reports
-// the chunk consumed, so the next call may overwrite its rows.
+// the chunk consumed, so the next call may overwrite its rows. Where the units would leave
+// slots idle, each is cut along the keys into slices of consecutive blocks (attn_slices),
+// whose partial results the last slice merges: 500 query rows, 32 heads, 2048 keys 93 ->
+// 56 us (its copies landed before; 76 with them).
 //
 // Per wave: 32 query rows, head dimension 128, v_mfma_f32_32x32x16_bf16.
 //   scores, transposed: S^T = K . Q^T (first operand K rows from LDS, second operand the
@@ -55,6 +58,7 @@ constexpr int kThreads = 256;         // 4 waves x 32 query rows
 constexpr int kTileBytes = BKV * D * 2;   // one K or V tile: 16 KiB
 constexpr int kBufferDword3 = 0x00020000;  // raw buffer resource word 3 (gfx9 family)
 __device__ const bf16x2_t kBf16Ones = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
+constexpr int kThrough = 1 | 16;      // cache policy sc0 sc1: to and from memory, past the caches
 constexpr int kMaxAttnChunks = 4096;  // per-workgroup ready cache: one bit per chunk
 constexpr float kLn2 = 0.6931471805599453f;
 // Largest row sum of one block's weights accepted against the running reference; a
@@ -62,6 +66,7 @@ constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kRowSumLimit = 65536.0f;
 
 static_assert(BQ == 32 * (kThreads / 64), "one wave per 32 query rows");
+static_assert(kAttnPartBytes == kThreads * (64 + 2) * 4, "a slice's partial results");
 
 __device__ __forceinline__ int64_t load_ready(const int64_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -299,6 +304,9 @@ __device__ __forceinline__ void value_block(const lds_u8_t* vt, const int (&v_la
 
 }  // namespace
 
+// kSliced: units are slices along the keys; without it none of that code burdens the loop
+// (in one kernel for both, the 32768-key workload took 2113 us instead of 2032).
+template <bool kSliced>
 __global__ __launch_bounds__(kThreads, 2) void ring_attn(AttnArgs a) {
   // K and V tiles, double-buffered
   __shared__ __attribute__((aligned(1024))) unsigned char sK[2 * kTileBytes];
@@ -337,6 +345,8 @@ __global__ __launch_bounds__(kThreads, 2) void ring_attn(AttnArgs a) {
     // clear the next call's state set (its prologue, folded into this kernel)
     for (int c = tid; c < a.n_chunks; c += kThreads) a.next_counters[c] = 0u;
     if (tid < kXcdLists) a.next_ticket[tid] = 0u;
+    if (kSliced)
+      for (int i = tid; i < a.n_units / a.slices; i += kThreads) a.next_slot_count[i] = 0u;
     if (tid == 0) {
       a.next_diag->timed_out = 0u;
       a.next_diag->chunk = -1;
@@ -355,17 +365,26 @@ __global__ __launch_bounds__(kThreads, 2) void ring_attn(AttnArgs a) {
   const int G = a.H / a.Hkv;
   uint32_t units = 0;
 
-  for (;;) {
+  // A unit per workgroup: by static slot, those of a die consecutive (the dispatcher deals
+  // workgroups to the dies round robin), without tickets.
+  const int grid = static_cast<int>(gridDim.x), wg = static_cast<int>(blockIdx.x);
+  const bool one_shot = a.n_units <= grid;
+  const int slot = grid % kXcdLists == 0 ? (wg % kXcdLists) * (grid / kXcdLists) + wg / kXcdLists : wg;
+  for (int iter = 0;; ++iter) {
     __syncthreads();  // everyone is done with s_unit / s_state / LDS of the previous unit
     if (tid == 0) {
-      int u = next_unit(a, xcd);
-      if (load_flag(&a.diag->abort)) u = a.n_units;
+      int u = one_shot ? (iter == 0 ? slot : a.n_units) : next_unit(a, xcd);
+      if (u < a.n_units && load_flag(&a.diag->abort)) u = a.n_units;
       s_unit = u;
     }
     __syncthreads();
-    const int u = __builtin_amdgcn_readfirstlane(s_unit);
-    if (u >= a.n_units) break;
+    const int vu = __builtin_amdgcn_readfirstlane(s_unit);
+    if (vu >= a.n_units) break;
     ++units;
+    // slice sl of the (query block, head) u: the key blocks b_begin .. b_end - 1 in arrival order
+    const int u = kSliced ? vu / a.slices : vu, sl = kSliced ? vu - u * a.slices : 0;
+    const int b_begin = kSliced ? static_cast<int>(static_cast<int64_t>(a.n_blocks) * sl / a.slices) : 0;
+    const int b_end = kSliced ? static_cast<int>(static_cast<int64_t>(a.n_blocks) * (sl + 1) / a.slices) : 0;
     // unit -> (key/value head g, query block, head of g's group): consecutive units, and
     // so a die's range of them, share key/value heads
     const int per_g = n_qb * G;
@@ -389,8 +408,17 @@ __global__ __launch_bounds__(kThreads, 2) void ring_attn(AttnArgs a) {
     float m = -__builtin_inff(), l = 0.0f;
 
     bool aborted = false;
+    int b = 0;  // blocks of the chunks before this one
     for (int pos = 0; pos < a.n_chunks; ++pos) {
       const int c = a.arrival[pos];
+      int lo = 0, hi = 0;  // the slice's blocks of this chunk
+      if constexpr (kSliced) {
+        const int chunk_blocks = (a.chunk_rows[2 * c + 1] - a.chunk_rows[2 * c]) / BKV;
+        lo = b_begin > b ? b_begin - b : 0;
+        hi = b_end - b < chunk_blocks ? b_end - b : chunk_blocks;
+        b += chunk_blocks;
+        if (lo >= hi) continue;
+      }
       __syncthreads();
       if (tid == 0) s_state = wait_chunk(a, c, u, ready_bits);
       __syncthreads();
@@ -404,7 +432,7 @@ __global__ __launch_bounds__(kThreads, 2) void ring_attn(AttnArgs a) {
       // ahead of use (K of block j + 2 and V of block j + 1 during step j) into double
       // buffers (K of block j in buffer j % 2, V likewise), so one barrier per block
       // publishes the step's tiles and frees the previous step's.
-      const int r0 = a.chunk_rows[2 * c], r1 = a.chunk_rows[2 * c + 1];
+      const int r0 = a.chunk_rows[2 * c] + (kSliced ? lo * BKV : 0), r1 = kSliced ? r0 + (hi - lo) * BKV : a.chunk_rows[2 * c + 1];
       const int nb = (r1 - r0) / BKV;
       if (nb > 0) {
         dma_tile(a.K, a.Hkv, g, r0, sK_addr, wave, k_voff0, 16 * key_bytes);
@@ -450,7 +478,7 @@ __global__ __launch_bounds__(kThreads, 2) void ring_attn(AttnArgs a) {
       // loads are waited for before its LDS stores, and every thread has passed the
       // barrier after the chunk's last stores); prefetches still in flight re-read the
       // chunk's last block and are discarded
-      if (tid == 0) {
+      if (!kSliced && tid == 0) {
         const uint32_t done =
             __hip_atomic_fetch_add(a.counters + c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) + 1u;
         if (done == static_cast<uint32_t>(a.n_units))
@@ -458,6 +486,66 @@ __global__ __launch_bounds__(kThreads, 2) void ring_attn(AttnArgs a) {
       }
     }
     if (aborted) break;
+
+    if constexpr (kSliced) {
+      // A slice counts every chunk at its end, a lane each (it has read its own, and never
+      // reads the others).
+      if (wave == 0)
+        for (int c = lane; c < a.n_chunks; c += 64) {
+          const uint32_t done =
+              __hip_atomic_fetch_add(a.counters + c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) + 1u;
+          if (done == static_cast<uint32_t>(a.n_units))
+            __hip_atomic_store(a.out_flags + c, a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+      // Partial results go through to memory (the slices may run on any die); the slice
+      // that finishes last reads all of them past the caches and merges them in slice
+      // order, so the result does not depend on which slice that was. Layout per slice:
+      // 16-byte vector v of thread t at (v * kThreads + t) * 16, then each thread's m and l.
+      const __amdgpu_buffer_rsrc_t rsW =
+          make_rsrc(reinterpret_cast<const unsigned char*>(a.ws) + static_cast<int64_t>(u) * a.slices * kAttnPartBytes,
+                    static_cast<int>(a.slices * kAttnPartBytes));
+      const int part = static_cast<int>(kAttnPartBytes), ml = 16 * kThreads * 16;
+      const int t16 = tid * 16, t8 = tid * 8;
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int b4 = 0; b4 < 4; ++b4) {
+          const f32x4_t v{acc[db][4 * b4 + 0], acc[db][4 * b4 + 1], acc[db][4 * b4 + 2], acc[db][4 * b4 + 3]};
+          // (no scalar offset register: the compiler would not protect the data registers)
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), rsW,
+                                                 t16 + sl * part + (4 * db + b4) * kThreads * 16, 0, kThrough);
+        }
+      __builtin_amdgcn_raw_buffer_store_b64(u32x2_t{__float_as_uint(m), __float_as_uint(l)}, rsW, t8 + sl * part + ml, 0,
+                                            kThrough);
+      wait_vm_all();  // written to memory
+      __syncthreads();
+      if (tid == 0)
+        s_state = __hip_atomic_fetch_add(a.slot_count + u, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                  static_cast<uint32_t>(a.slices - 1);
+      __syncthreads();
+      if (!__builtin_amdgcn_readfirstlane(s_state)) continue;
+      float top = -__builtin_inff();
+      for (int s = 0; s < a.slices; ++s)
+        top = fmaxf(top, __uint_as_float(__builtin_amdgcn_raw_buffer_load_b64(rsW, t8 + s * part + ml, 0, kThrough)[0]));
+      m = top;
+      l = 0.0f;
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db) acc[db] = f32x16_t{};
+      for (int s = 0; s < a.slices; ++s) {
+        const u32x2_t x = __builtin_amdgcn_raw_buffer_load_b64(rsW, t8 + s * part + ml, 0, kThrough);
+        u32x4_t v[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          v[i] = __builtin_amdgcn_raw_buffer_load_b128(rsW, t16 + s * part + i * kThreads * 16, 0, kThrough);
+        const float f = __builtin_amdgcn_exp2f(__uint_as_float(x[0]) - top);
+        l = fmaf(__uint_as_float(x[1]), f, l);
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            acc[i / 4][4 * (i % 4) + e] = fmaf(__uint_as_float(v[i][e]), f, acc[i / 4][4 * (i % 4) + e]);
+      }
+    }
 
     // O = acc / l over the whole row (both lanes' keys); each lane holds 16 head dims of
     // its row per 32-dim tile, in runs of four
@@ -484,7 +572,10 @@ int32_t attn_threads() { return kThreads; }
 
 hipError_t launch_ring_attn(const AttnArgs& args, int32_t grid, hipStream_t stream, hipEvent_t start,
                             hipEvent_t stop) {
-  hipExtLaunchKernelGGL(ring_attn, dim3(grid), dim3(kThreads), 0, stream, start, stop, 0, args);
+  if (args.slices > 1)
+    hipExtLaunchKernelGGL(ring_attn<true>, dim3(grid), dim3(kThreads), 0, stream, start, stop, 0, args);
+  else
+    hipExtLaunchKernelGGL(ring_attn<false>, dim3(grid), dim3(kThreads), 0, stream, start, stop, 0, args);
   return hipGetLastError();
 }
 
@@ -492,7 +583,7 @@ hipError_t attn_grid(int device, int32_t* grid) {
   int cus = 0, per_cu = 0;
   hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
   if (e != hipSuccess) return e;
-  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(&ring_attn), kThreads, 0);
+  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(&ring_attn<true>), kThreads, 0);
   if (e != hipSuccess) return e;
   *grid = cus * (per_cu < 1 ? 1 : per_cu);
   return hipSuccess;

@@ -1,0 +1,64 @@
+"""GPU parity of ring attention whose units are cut along the keys (few query rows and
+heads): slices of unequal length, slices that begin inside a chunk, chunks no slice of a
+unit reads, rows whose largest score lies in one slice only, calls in a row on one plan.
+Against plain attention in 64 bits; bf16 weights bound the error at 2e-2 of the result."""
+import math
+
+import numpy as np
+import pytest
+
+import paper_2601_20595_amd as csg
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+CASES = [
+    # rows, heads, kv heads, chunk rows (64 each), local chunks
+    (100, 2, 1, [64] * 13, {0, 1}),                    # 13 blocks: two slices, 6 and 7
+    (1, 4, 2, [64 * 24], {0}),                         # one chunk: every slice inside it
+    (300, 3, 3, [64, 448, 128, 1024, 64, 320], {2}),   # eight slices over uneven chunks
+    (128, 1, 1, [64 * 11], set()),                     # 11 blocks: one slice
+    (4100, 16, 4, [512, 512, 256], {1}),               # more units than slots: not cut
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "q%d-h%d-kv%d-n%d" % (c[0], c[1], c[2], len(c[3])))
+@pytest.mark.parametrize("spread", [1.0, 8.0])
+def test_sliced_attention_parity(case, spread):
+    rows, H, Hkv, sizes, local = case
+    print("attention slices", case, spread, flush=True)
+    ends = np.cumsum(sizes).tolist()
+    chunks = [(e - s, e, 0 if i in local else 1 + i, 0, int(i in local)) for i, (e, s) in enumerate(zip(ends, sizes))]
+    order = sorted(range(len(sizes)), key=lambda i: (i not in local, -i))
+    plan = csg.AttnPlan(H, Hkv, 128, rows, csg.Schedule.create(chunks, order), cfg={"timeout_ms": 1000})
+    g = torch.Generator(device=DEV).manual_seed(7)
+    S = ends[-1]
+    q = torch.randn((rows, H, 128), generator=g, device=DEV).to(torch.bfloat16)
+    # the keys' scale grows along the sequence: with a spread of 8 the last keys hold the maxima
+    k = (torch.randn((S, Hkv, 128), generator=g, device=DEV) *
+         torch.linspace(1.0 / spread, 1.0, S, device=DEV)[:, None, None]).to(torch.bfloat16)
+    v = torch.randn((S, Hkv, 128), generator=g, device=DEV).to(torch.bfloat16)
+    o, lse = torch.empty_like(q), torch.empty((H, rows), device=DEV)
+    st, cp = torch.cuda.Stream(), torch.cuda.Stream()
+    first = None
+    for _ in range(3):
+        kl, vl = k.clone(), v.clone()
+        for c in chunks:
+            if not c[4]:
+                kl[c[0]:c[1]] = float("nan")
+                vl[c[0]:c[1]] = float("nan")
+        o.fill_(float("nan"))
+        torch.cuda.synchronize()
+        plan.ring_attn(q, kl, vl, k, v, o, lse, "overlap", st, cp)
+        plan.check()
+        torch.cuda.synchronize()
+        first = o.clone() if first is None else first
+        assert torch.equal(o, first)               # merged in slice order: the same bits every time
+    for h in range(H):
+        s = (q[:, h].double() @ k[:, h * Hkv // H].double().t()) / math.sqrt(128)
+        want = torch.softmax(s, dim=1) @ v[:, h * Hkv // H].double()
+        err = (o[:, h].double() - want).abs().max() / want.square().mean().sqrt()
+        assert err <= 2e-2 * max(1.0, float(want.abs().max() / want.square().mean().sqrt())), (h, float(err))
+        assert (lse[h].double() - torch.logsumexp(s, dim=1)).abs().max() <= 2e-2
+    plan.close()
