@@ -206,7 +206,10 @@ struct csg_plan {
   hipEvent_t ev_copy_in = nullptr;     // the caller's copy stream reached the call
   hipEvent_t ev_prologue = nullptr;    // the latest prologue finished
   bool prologue_queued = false;        // ev_prologue has been recorded
-  hipEvent_t ev_kernel_done[2] = {nullptr, nullptr};  // by epoch parity
+  // Completion of the latest kernel by epoch parity: the stop event of its launch (one of
+  // ev_k1), which the dispatch itself completes. A marker recorded behind the kernel would
+  // cost the stream a barrier and a cache flush of its own at every call.
+  hipEvent_t ev_kernel_done[2] = {nullptr, nullptr};
   hipEvent_t ev_k0[kTimingRing] = {};  // timing events around each kernel launch (ring)
   hipEvent_t ev_k1[kTimingRing] = {};
   uint64_t n_launches = 0;
@@ -273,7 +276,7 @@ void free_plan_device(csg_plan* p) {
                     static_cast<void*>(p->d_trace), static_cast<void*>(p->d_kready)})
     if (ptr) (void)hipFree(ptr);
   if (p->h_out_flags) (void)hipHostFree(p->h_out_flags);
-  for (hipEvent_t e : {p->ev_copy_in, p->ev_prologue, p->ev_kernel_done[0], p->ev_kernel_done[1]})
+  for (hipEvent_t e : {p->ev_copy_in, p->ev_prologue})
     if (e) (void)hipEventDestroy(e);
   for (int i = 0; i < kTimingRing; ++i) {
     if (p->ev_k0[i]) (void)hipEventDestroy(p->ev_k0[i]);
@@ -517,7 +520,6 @@ csg_status setup_device(csg_plan* p) {
   if ((st = tables.commit(&p->d_tables)) != CSG_OK) return st;
   CSG_HIP(hipEventCreateWithFlags(&p->ev_copy_in, hipEventDisableTiming));
   CSG_HIP(hipEventCreateWithFlags(&p->ev_prologue, hipEventDisableTiming));
-  for (hipEvent_t& e : p->ev_kernel_done) CSG_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   for (int i = 0; i < kTimingRing; ++i) {
     CSG_HIP(hipEventCreate(&p->ev_k0[i]));
     CSG_HIP(hipEventCreate(&p->ev_k1[i]));
@@ -808,7 +810,7 @@ csg_status launch_gemm(csg_plan* p, const void* A, const void* B, void* C, csg_m
   CSG_HIP(csg::launch_chunk_gemm(p->key, a, grid, compute, p->ev_k0[slot], p->ev_k1[slot]));
   p->reset_for_epoch = a.next_ticket ? p->epoch + 1 : 0;
   ++p->n_launches;
-  CSG_HIP(hipEventRecord(p->ev_kernel_done[p->epoch & 1], compute));
+  p->ev_kernel_done[p->epoch & 1] = p->ev_k1[slot];
   p->kernel_pending[p->epoch & 1] = true;
   p->last_kernel_epoch = p->epoch;
   return CSG_OK;
@@ -1025,7 +1027,6 @@ csg_status setup_attn_device(csg_plan* p) {
   if ((st = tables.commit(&p->d_tables)) != CSG_OK) return st;
   CSG_HIP(hipEventCreateWithFlags(&p->ev_copy_in, hipEventDisableTiming));
   CSG_HIP(hipEventCreateWithFlags(&p->ev_prologue, hipEventDisableTiming));
-  for (hipEvent_t& e : p->ev_kernel_done) CSG_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   for (int i = 0; i < kTimingRing; ++i) {
     CSG_HIP(hipEventCreate(&p->ev_k0[i]));
     CSG_HIP(hipEventCreate(&p->ev_k1[i]));
@@ -1075,7 +1076,7 @@ csg_status launch_attn(csg_plan* p, const void* q, const void* k, const void* v,
   p->reset_for_epoch = p->epoch + 1;
   p->expected_units = static_cast<uint32_t>(p->n_units);
   ++p->n_launches;
-  CSG_HIP(hipEventRecord(p->ev_kernel_done[p->epoch & 1], compute));
+  p->ev_kernel_done[p->epoch & 1] = p->ev_k1[slot];
   p->kernel_pending[p->epoch & 1] = true;
   p->last_kernel_epoch = p->epoch;
   return CSG_OK;
