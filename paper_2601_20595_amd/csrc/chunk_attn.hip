@@ -61,6 +61,7 @@ __device__ const bf16x2_t kBf16Ones = {static_cast<__bf16>(1.0f), static_cast<__
 constexpr int kThrough = 1 | 16;      // cache policy sc0 sc1: to and from memory, past the caches
 constexpr int kMaxAttnChunks = 4096;  // per-workgroup ready cache: one bit per chunk
 constexpr float kLn2 = 0.6931471805599453f;
+constexpr float kMaxFloat = 3.4028234663852886e38f;
 // Largest row sum of one block's weights accepted against the running reference; a
 // larger (or non-finite) sum moves the reference to the row's maximum instead.
 constexpr float kRowSumLimit = 65536.0f;
@@ -251,6 +252,7 @@ __device__ __forceinline__ float block_weights(const f32x16_t (&sc)[2], float sc
 // taken by the whole wave (with unchanged m on rows that do not need it), so its
 // cross-lane exchange runs with every lane active. Returns the factor by which the
 // accumulators are to be multiplied (1: unchanged); l is this lane's partial sum.
+template <bool kSliced>
 __device__ __forceinline__ float softmax_block(const f32x16_t (&sc)[2], float scale_log2, float& m, float& l,
                                                bf16x8_t (&pb)[4], bool& rescale) {
   float psum = block_weights(sc, scale_log2, m, pb);
@@ -265,7 +267,9 @@ __device__ __forceinline__ float softmax_block(const f32x16_t (&sc)[2], float sc
 #pragma unroll
       for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[kb][r]);
     mx = max_halves(mx) * scale_log2;  // the scale is positive
-    const float m_new = move ? fmaxf(m, mx) : m;
+    // (a slice may hold nothing but scores of -inf, whose reference has to stay finite: its
+    // sums are then 0, where exp2(-inf - -inf) would make the whole row NaN)
+    const float m_new = move ? fmaxf(m, kSliced ? fmaxf(mx, -kMaxFloat) : mx) : m;
     alpha = __builtin_amdgcn_exp2f(m - m_new);  // 0 on a unit's first block, 1 on unmoved rows
     m = m_new;
     l *= alpha;
@@ -458,7 +462,7 @@ __global__ __launch_bounds__(kThreads, 2) void ring_attn(AttnArgs a) {
           score_block(sK + nbuf * kTileBytes + k_even, sK + nbuf * kTileBytes + k_odd, qf, nxt);
           bf16x8_t pb[4];
           bool rescale;
-          const float alpha = softmax_block(cur, a.scale_log2, m, l, pb, rescale);
+          const float alpha = softmax_block<kSliced>(cur, a.scale_log2, m, l, pb, rescale);
           if (rescale) {
 #pragma unroll
             for (int db = 0; db < D / 32; ++db) acc[db] *= alpha;

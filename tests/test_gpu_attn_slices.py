@@ -62,3 +62,32 @@ def test_sliced_attention_parity(case, spread):
         assert err <= 2e-2 * max(1.0, float(want.abs().max() / want.square().mean().sqrt())), (h, float(err))
         assert (lse[h].double() - torch.logsumexp(s, dim=1)).abs().max() <= 2e-2
     plan.close()
+
+
+def test_slices_of_keys_that_score_minus_infinity_count_for_nothing():
+    """Keys from the third slice on score -inf for every query: their slices have no finite
+    maximum, and the result is that of the other keys."""
+    rows, H, sizes = 128, 2, [64 * 12, 64 * 36]
+    print("attention slices, -inf scores", flush=True)
+    chunks = [(0, sizes[0], 0, 0, 1), (sizes[0], sum(sizes), 1, 0, 0)]
+    plan = csg.AttnPlan(H, 1, 128, rows, csg.Schedule.create(chunks, [0, 1]), cfg={"timeout_ms": 1000})
+    g = torch.Generator(device=DEV).manual_seed(9)
+    q = torch.randn((rows, H, 128), generator=g, device=DEV).to(torch.bfloat16)
+    q[:, :, 0] = q[:, :, 0].abs() + 0.5
+    k = torch.randn((sum(sizes), 1, 128), generator=g, device=DEV).to(torch.bfloat16)
+    v = torch.randn((sum(sizes), 1, 128), generator=g, device=DEV).to(torch.bfloat16)
+    k[sizes[0]:, :, 0] = float("-inf")
+    o, lse = torch.empty_like(q), torch.empty((H, rows), device=DEV)
+    st, cp = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    plan.ring_attn(q, k.clone(), v.clone(), k, v, o, lse, "overlap", st, cp)
+    plan.check()
+    torch.cuda.synchronize()
+    n = sizes[0]
+    for h in range(H):
+        s = (q[:, h].double() @ k[:n, 0].double().t()) / math.sqrt(128)
+        want = torch.softmax(s, dim=1) @ v[:n, 0].double()
+        scale = float(want.square().mean().sqrt())
+        assert (o[:, h].double() - want).abs().max() <= 2e-2 * max(scale, float(want.abs().max()))
+        assert (lse[h].double() - torch.logsumexp(s, dim=1)).abs().max() <= 2e-2
+    plan.close()
