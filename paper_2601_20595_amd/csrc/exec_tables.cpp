@@ -181,6 +181,7 @@ Geometry choose_geometry(bool bf16, const std::vector<int64_t>& group_rows, int6
   static const int32_t kSlices[] = {1, 2, 3, 4, 6, 8};
   const int64_t steps = K / (bf16 ? 64 : 16);
   Geometry best;
+  if (slots < 1) return best;  // every slot copies: whole tiles
   double best_us = 0.0;
   for (const Tile& x : kTiles) {
     if (x.bf16 != bf16 || x.bn < min_bn) continue;

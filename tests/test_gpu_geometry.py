@@ -19,6 +19,8 @@ CASES = [
     ("ag", 2, 512, 4, 1796, 2048, "f32", {}),        # 128 x 128 tiles
     ("ag", 2, 2048, 4, 1792, 4096, "bf16", {}),      # 256 x 256 tiles in two slices
     ("ag", 2, 300, 1, 1228, 2048, "bf16", {"copy_backend": "kernel", "copy_workgroups": 9}),
+    ("ag", 2, 300, 1, 260, 640, "bf16", {"copy_backend": "kernel", "copy_workgroups": 249}),  # a copier in every slot
+    ("ag", 2, 300, 1, 260, 640, "bf16", {"copy_backend": "kernel", "copy_workgroups": 256}),
     ("ag", 2, 300, 2, 520, 640, "bf16", {"intra_order": 1, "tile_dispatch": 2}),
     ("rs", 2, 64, 2, 516, 2048, "bf16", {}),
     ("rs", 2, 640, 2, 1032, 512, "f32", {}),
@@ -29,6 +31,7 @@ CASES = [
     ("grouped", 4, 0, 0, 1028, 256, "f32", {}),
     ("noalloc", 8, 16, 1, 1792, 4096, "bf16", {}),
     ("noalloc", 2, 300, 3, 260, 1088, "f32", {}),
+    ("noalloc", 2, 300, 1, 260, 640, "bf16", {"copy_workgroups": 256}),
 ]
 
 
@@ -71,7 +74,7 @@ def test_cut_launches_bit_exact(case):
                     land[x[0]:x[1]] = float("nan")
             torch.cuda.synchronize()
             if op == "noalloc":
-                csg.csg_ag_gemm_noalloc(sched, M, N, K, "bf16", out, land, a, b, c, "overlap", stream=st)
+                csg.csg_ag_gemm_noalloc(sched, M, N, K, "bf16", out, land, a, b, c, "overlap", cfg.get("copy_workgroups", 0), stream=st)
             else:
                 (plan.ag_gemm if op == "ag" else plan.grouped_gemm)(land, a, b, c, "overlap", st, cp)
         else:
