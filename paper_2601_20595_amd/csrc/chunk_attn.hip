@@ -243,6 +243,16 @@ __device__ __forceinline__ float block_weights(const f32x16_t (&sc)[2], float sc
   return psum;
 }
 
+// The largest scaled score of a block in the lane's query row.
+__device__ __forceinline__ float row_max(const f32x16_t (&sc)[2], float scale_log2) {
+  float mx = -__builtin_inff();
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[kb][r]);
+  return max_halves(mx) * scale_log2;  // the scale is positive
+}
+
 // Online softmax of one block. The running reference m of a query row moves only when
 // it must: the block's weights are first taken against the current m, and only if the
 // row's sum of them exceeds kRowSumLimit (or is not finite, as on a unit's first block,
@@ -261,12 +271,7 @@ __device__ __forceinline__ float softmax_block(const f32x16_t (&sc)[2], float sc
   float alpha = 1.0f;
   rescale = __builtin_amdgcn_ballot_w64(move) != 0;
   if (rescale) {
-    float mx = -__builtin_inff();
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[kb][r]);
-    mx = max_halves(mx) * scale_log2;  // the scale is positive
+    const float mx = row_max(sc, scale_log2);
     // (a slice may hold nothing but scores of -inf, whose reference has to stay finite: its
     // sums are then 0, where exp2(-inf - -inf) would make the whole row NaN)
     const float m_new = move ? fmaxf(m, kSliced ? fmaxf(mx, -kMaxFloat) : mx) : m;
@@ -410,6 +415,10 @@ __global__ __launch_bounds__(kThreads, 2) void ring_attn(AttnArgs a) {
 #pragma unroll
     for (int db = 0; db < D / 32; ++db) acc[db] = f32x16_t{};
     float m = -__builtin_inff(), l = 0.0f;
+    // A slice but the first takes its reference from the scores of the unit's first block,
+    // as the uncut unit does, so that both round the same weights to bf16 (with each
+    // slice's own first block as its reference, results moved by 3e-3 of their norm).
+    bool seed = kSliced && sl > 0;
 
     bool aborted = false;
     int b = 0;  // blocks of the chunks before this one
@@ -424,7 +433,11 @@ __global__ __launch_bounds__(kThreads, 2) void ring_attn(AttnArgs a) {
         if (lo >= hi) continue;
       }
       __syncthreads();
-      if (tid == 0) s_state = wait_chunk(a, c, u, ready_bits);
+      if (tid == 0) {
+        int state = wait_chunk(a, c, u, ready_bits);
+        if (seed && state >= 0) state = wait_chunk(a, a.arrival[0], u, ready_bits);
+        s_state = state;
+      }
       __syncthreads();
       if (__builtin_amdgcn_readfirstlane(s_state) < 0) {
         aborted = true;
@@ -442,6 +455,9 @@ __global__ __launch_bounds__(kThreads, 2) void ring_attn(AttnArgs a) {
         dma_tile(a.K, a.Hkv, g, r0, sK_addr, wave, k_voff0, 16 * key_bytes);
         dma_tile(a.V, a.Hkv, g, r0, sV_addr, wave, v_voff0, 4 * key_bytes);
         if (nb > 1) dma_tile(a.K, a.Hkv, g, r0 + BKV, sK_addr + kTileBytes, wave, k_voff0, 16 * key_bytes);
+        // (the first block's keys go where V of block 1 goes from the first step on)
+        if (seed)
+          dma_tile(a.K, a.Hkv, g, a.chunk_rows[2 * a.arrival[0]], sV_addr + kTileBytes, wave, k_voff0, 16 * key_bytes);
         wait_vm_all();
         __syncthreads();
         // One step: block j's softmax and value product, block j + 1's scores. The scores
@@ -470,6 +486,11 @@ __global__ __launch_bounds__(kThreads, 2) void ring_attn(AttnArgs a) {
           value_block(sV_lds + buf * kTileBytes, v_lane, pb, acc);
         };
         f32x16_t sa[2], sb[2];
+        if (seed) {
+          score_block(sV + kTileBytes + k_even, sV + kTileBytes + k_odd, qf, sa);
+          m = fmaxf(row_max(sa, a.scale_log2), -kMaxFloat);
+          seed = false;
+        }
         score_block(sK + k_even, sK + k_odd, qf, sa);
         int j = 0;
         for (; j + 1 < nb; j += 2) {

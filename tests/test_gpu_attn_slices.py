@@ -91,3 +91,58 @@ def test_slices_of_keys_that_score_minus_infinity_count_for_nothing():
         assert (o[:, h].double() - want).abs().max() <= 2e-2 * max(scale, float(want.abs().max()))
         assert (lse[h].double() - torch.logsumexp(s, dim=1)).abs().max() <= 2e-2
     plan.close()
+
+
+SAME = [
+    # rows, heads, kv heads, chunk rows, local chunks, arrival order
+    (500, 32, 8, [256] * 8, {4, 5}, [4, 5, 6, 7, 0, 1, 2, 3]),   # four slices
+    (300, 3, 3, [64, 448, 128, 1024, 64, 320], set(), [3, 0, 5, 1, 4, 2]),  # eight; the first chunk arrives too
+    (64, 2, 1, [64 * 12], {0}, [0]),                             # two slices of one chunk
+]
+
+
+@pytest.mark.parametrize("case", SAME, ids=lambda c: "q%d-h%d-kv%d-n%d" % (c[0], c[1], c[2], len(c[3])))
+def test_slices_weigh_the_keys_as_the_uncut_kernel_does(case):
+    """The same plan cut and uncut (num_workgroups named). Both round the same weights to
+    bf16, so only the order of the fp32 sums differs: n keys in sums of fewer than n terms
+    keep a relative error below n 2^-24 (about 1e-4 here; a few 1e-7 as errors average),
+    which moves few results across a bf16 boundary and none further than to its
+    neighbour."""
+    rows, H, Hkv, sizes, local, order = case
+    print("attention slices, cut and uncut", case, flush=True)
+    ends = np.cumsum(sizes).tolist()
+    S = ends[-1]
+    chunks = [(e - s, e, 0 if i in local else 1 + i, 0, int(i in local)) for i, (e, s) in enumerate(zip(ends, sizes))]
+    g = torch.Generator(device=DEV).manual_seed(11)
+    q = torch.randn((rows, H, 128), generator=g, device=DEV).to(torch.bfloat16)
+    k = torch.randn((S, Hkv, 128), generator=g, device=DEV).to(torch.bfloat16)
+    v = torch.randn((S, Hkv, 128), generator=g, device=DEV).to(torch.bfloat16)
+    st, cp = torch.cuda.Stream(), torch.cuda.Stream()
+    out, units = [], []
+    for cfg in ({"timeout_ms": 1000}, {"timeout_ms": 1000, "num_workgroups": 256}):
+        plan = csg.AttnPlan(H, Hkv, 128, rows, csg.Schedule.create(chunks, order), cfg=cfg)
+        o, lse = torch.empty_like(q), torch.empty((H, rows), device=DEV)
+        kl, vl = k.clone(), v.clone()
+        for c in chunks:
+            if not c[4]:
+                kl[c[0]:c[1]] = float("nan")
+                vl[c[0]:c[1]] = float("nan")
+        torch.cuda.synchronize()
+        plan.ring_attn(q, kl, vl, k, v, o, lse, "overlap", st, cp)
+        plan.check()
+        torch.cuda.synchronize()
+        out.append((o, lse))
+        units.append(plan.info.n_units)
+        plan.close()
+    whole = (rows + 127) // 128 * H
+    assert units[1] == whole and units[0] > whole          # the first plan is cut
+    (o, lse), (uo, ulse) = out
+    assert float((lse - ulse).abs().max()) <= S * 2.0 ** -24
+    differ = (o != uo)
+    print("differ", float(differ.float().mean()), "rel", float((o.double() - uo.double()).norm() / uo.double().norm()),
+          "lse", float((lse - ulse).abs().max()), flush=True)
+    # a sum's error of e moves it across a boundary with a chance of about e / 2^-9: 1e-3
+    # of the results for 2e-6, ten times as many where terms of either sign cancel
+    assert float(differ.float().mean()) <= 1e-2
+    rms = float(uo.double().square().mean().sqrt())
+    assert float(((o.double() - uo.double()).abs() / uo.double().abs().clamp(min=rms)).max()) <= 2.0 ** -7
