@@ -243,14 +243,16 @@ __device__ __forceinline__ float block_weights(const f32x16_t (&sc)[2], float sc
   return psum;
 }
 
-// The largest scaled score of a block in the lane's query row.
+// The reference that a block gives the lane's query row: its largest scaled score, and a
+// finite value where all of them are -inf, so that their weights are 0 (against -inf
+// itself they would be exp2(-inf - -inf), and the whole row NaN).
 __device__ __forceinline__ float row_max(const f32x16_t (&sc)[2], float scale_log2) {
   float mx = -__builtin_inff();
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
     for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[kb][r]);
-  return max_halves(mx) * scale_log2;  // the scale is positive
+  return fmaxf(max_halves(mx) * scale_log2, -kMaxFloat);  // the scale is positive
 }
 
 // Online softmax of one block. The running reference m of a query row moves only when
@@ -262,7 +264,6 @@ __device__ __forceinline__ float row_max(const f32x16_t (&sc)[2], float scale_lo
 // taken by the whole wave (with unchanged m on rows that do not need it), so its
 // cross-lane exchange runs with every lane active. Returns the factor by which the
 // accumulators are to be multiplied (1: unchanged); l is this lane's partial sum.
-template <bool kSliced>
 __device__ __forceinline__ float softmax_block(const f32x16_t (&sc)[2], float scale_log2, float& m, float& l,
                                                bf16x8_t (&pb)[4], bool& rescale) {
   float psum = block_weights(sc, scale_log2, m, pb);
@@ -272,9 +273,7 @@ __device__ __forceinline__ float softmax_block(const f32x16_t (&sc)[2], float sc
   rescale = __builtin_amdgcn_ballot_w64(move) != 0;
   if (rescale) {
     const float mx = row_max(sc, scale_log2);
-    // (a slice may hold nothing but scores of -inf, whose reference has to stay finite: its
-    // sums are then 0, where exp2(-inf - -inf) would make the whole row NaN)
-    const float m_new = move ? fmaxf(m, kSliced ? fmaxf(mx, -kMaxFloat) : mx) : m;
+    const float m_new = move ? fmaxf(m, mx) : m;
     alpha = __builtin_amdgcn_exp2f(m - m_new);  // 0 on a unit's first block, 1 on unmoved rows
     m = m_new;
     l *= alpha;
@@ -478,7 +477,7 @@ __global__ __launch_bounds__(kThreads, 2) void ring_attn(AttnArgs a) {
           score_block(sK + nbuf * kTileBytes + k_even, sK + nbuf * kTileBytes + k_odd, qf, nxt);
           bf16x8_t pb[4];
           bool rescale;
-          const float alpha = softmax_block<kSliced>(cur, a.scale_log2, m, l, pb, rescale);
+          const float alpha = softmax_block(cur, a.scale_log2, m, l, pb, rescale);
           if (rescale) {
 #pragma unroll
             for (int db = 0; db < D / 32; ++db) acc[db] *= alpha;
@@ -488,7 +487,7 @@ __global__ __launch_bounds__(kThreads, 2) void ring_attn(AttnArgs a) {
         f32x16_t sa[2], sb[2];
         if (seed) {
           score_block(sV + kTileBytes + k_even, sV + kTileBytes + k_odd, qf, sa);
-          m = fmaxf(row_max(sa, a.scale_log2), -kMaxFloat);
+          m = row_max(sa, a.scale_log2);
           seed = false;
         }
         score_block(sK + k_even, sK + k_odd, qf, sa);

@@ -146,3 +146,36 @@ def test_slices_weigh_the_keys_as_the_uncut_kernel_does(case):
     assert float(differ.float().mean()) <= 1e-2
     rms = float(uo.double().square().mean().sqrt())
     assert float(((o.double() - uo.double()).abs() / uo.double().abs().clamp(min=rms)).max()) <= 2.0 ** -7
+
+
+@pytest.mark.parametrize("rows,num_workgroups", [(128, 0), (128, 64), (9000, 0)], ids=["cut", "uncut", "uncut-rows"])
+@pytest.mark.parametrize("first", [64, 64 * 12], ids=["block", "chunk"])
+def test_first_keys_that_score_minus_infinity_count_for_nothing(rows, num_workgroups, first):
+    """The first keys to arrive score -inf for every query, alone and with the unit cut or
+    not: the result is that of the other keys, and does not depend on how a call is cut."""
+    H, sizes = 4, [64 * 24, first]
+    print("attention, -inf first", rows, num_workgroups, first, flush=True)
+    chunks = [(0, sizes[0], 0, 0, 1), (sizes[0], sum(sizes), 1, 0, 0)]
+    plan = csg.AttnPlan(H, 1, 128, rows, csg.Schedule.create(chunks, [1, 0]),
+                        cfg={"timeout_ms": 1000, "num_workgroups": num_workgroups})
+    assert (plan.info.n_units == (rows + 127) // 128 * H) == (num_workgroups != 0 or rows != 128)
+    g = torch.Generator(device=DEV).manual_seed(13)
+    q = torch.randn((rows, H, 128), generator=g, device=DEV).to(torch.bfloat16)
+    q[:, :, 0] = q[:, :, 0].abs() + 0.5
+    k = torch.randn((sum(sizes), 1, 128), generator=g, device=DEV).to(torch.bfloat16)
+    v = torch.randn((sum(sizes), 1, 128), generator=g, device=DEV).to(torch.bfloat16)
+    k[sizes[0]:, :, 0] = float("-inf")
+    o, lse = torch.empty_like(q), torch.empty((H, rows), device=DEV)
+    st, cp = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    plan.ring_attn(q, k.clone(), v.clone(), k, v, o, lse, "overlap", st, cp)
+    plan.check()
+    torch.cuda.synchronize()
+    n = sizes[0]
+    for h in range(H):
+        s = (q[:, h].double() @ k[:n, 0].double().t()) / math.sqrt(128)
+        want = torch.softmax(s, dim=1) @ v[:n, 0].double()
+        scale = float(want.square().mean().sqrt())
+        assert (o[:, h].double() - want).abs().max() <= 2e-2 * max(scale, float(want.abs().max()))
+        assert (lse[h].double() - torch.logsumexp(s, dim=1)).abs().max() <= 2e-2
+    plan.close()
