@@ -38,6 +38,8 @@ struct AttnArgs {
   int32_t n_chunks;
   const int32_t* arrival;     // [n_chunks]: chunk id at each arrival position
   const int32_t* chunk_rows;  // [2 * n_chunks] by chunk id: key row begin, end
+  const int32_t* first_block; // [n_chunks + 1] by arrival position: key blocks of the chunks before it
+  const int32_t* need;        // [n_chunks] by chunk id: units that read it, 0 if it is local (slices > 1)
   const int64_t* const* ready;  // per chunk id: 0 once its keys and values have landed
   uint32_t* counters;         // per chunk id: units done reading it
   uint32_t* out_flags;        // per chunk id: the call number once every unit has read it

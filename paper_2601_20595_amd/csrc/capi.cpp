@@ -199,6 +199,7 @@ struct csg_plan {
   int32_t at_slices = 1;               // key slices per (query block, head)
   int32_t* d_arrival = nullptr;        // [n_chunks] chunk id at each arrival position
   int32_t* d_chunk_rows = nullptr;     // [2 * n_chunks] key row begin / end by chunk id
+  int32_t* d_first_block = nullptr;    // [n_chunks + 1] key blocks before each arrival position
   const void* ar_partials = nullptr;  // this call's partials landing buffer
   bool copies_in_flight = false;       // a call returned before its copies completed (consumers:
                                        // error paths only; producer: every call)
@@ -993,6 +994,19 @@ csg_status setup_attn_device(csg_plan* p) {
   Arena state, tables;
   tables.add(&p->d_arrival, p->sched.order);
   tables.add(&p->d_chunk_rows, rows);
+  // key blocks before each arrival position, and per remote chunk the units that read it:
+  // the slices its blocks fall in, and of the first chunk to arrive every slice
+  std::vector<int32_t> first_block(1, 0), need(p->n_chunks(), 0);
+  const int64_t blocks = p->sched.total_rows / csg::kAttnBlockKV;
+  for (int32_t c : p->sched.order) {
+    const int64_t b0 = first_block.back(), b1 = b0 + (rows[2 * c + 1] - rows[2 * c]) / csg::kAttnBlockKV;
+    for (int64_t sl = 0; sl < p->at_slices && !p->sched.chunks[c].is_local; ++sl)
+      if (b0 == 0 || (blocks * sl / p->at_slices < b1 && blocks * (sl + 1) / p->at_slices > b0))
+        need[c] += static_cast<int32_t>(whole);
+    first_block.push_back(static_cast<int32_t>(b1));
+  }
+  tables.add(&p->d_need, need);
+  tables.add(&p->d_first_block, first_block);
   const size_t nflag = p->n_flags();
   state.add_zeros(&p->d_zero, 64);
   state.add_zeros(&p->d_counters, 2 * nflag * 4);
@@ -1060,6 +1074,8 @@ csg_status launch_attn(csg_plan* p, const void* q, const void* k, const void* v,
   a.n_chunks = p->n_chunks();
   a.arrival = p->d_arrival;
   a.chunk_rows = p->d_chunk_rows;
+  a.first_block = p->d_first_block;
+  a.need = p->d_need;
   a.ready = p->d_ready[set];
   a.counters = p->counters(set);
   a.out_flags = p->h_out_flags_dev;

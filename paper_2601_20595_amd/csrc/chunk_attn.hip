@@ -104,6 +104,16 @@ __device__ int wait_chunk(const AttnArgs& a, int c, int unit, uint32_t* ready_bi
   return 1;
 }
 
+// Counts a work unit that has read its part of chunk c; the last of the `need` units that
+// read the chunk reports it consumed (0: nobody asks, the chunk is local).
+__device__ __forceinline__ void count_chunk(const AttnArgs& a, int c, int need) {
+  if (need == 0) return;
+  const uint32_t done =
+      __hip_atomic_fetch_add(a.counters + c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) + 1u;
+  if (done == static_cast<uint32_t>(need))
+    __hip_atomic_store(a.out_flags + c, a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // K tile layout in LDS. Key row R (0..63) of the block has 16 pieces of 16 bytes (8
 // head dims each); logical piece p sits in 16-byte slot
 //     256 (p / 4) + 4 R + ((p % 4) ^ f(R)),   f(R) = ((R >> 2) ^ (R >> 1)) & 3.
@@ -420,15 +430,13 @@ __global__ __launch_bounds__(kThreads, 2) void ring_attn(AttnArgs a) {
     bool seed = kSliced && sl > 0;
 
     bool aborted = false;
-    int b = 0;  // blocks of the chunks before this one
     for (int pos = 0; pos < a.n_chunks; ++pos) {
       const int c = a.arrival[pos];
       int lo = 0, hi = 0;  // the slice's blocks of this chunk
       if constexpr (kSliced) {
-        const int chunk_blocks = (a.chunk_rows[2 * c + 1] - a.chunk_rows[2 * c]) / BKV;
-        lo = b_begin > b ? b_begin - b : 0;
-        hi = b_end - b < chunk_blocks ? b_end - b : chunk_blocks;
-        b += chunk_blocks;
+        const int b0 = a.first_block[pos], b1 = a.first_block[pos + 1];
+        lo = b_begin > b0 ? b_begin - b0 : 0;
+        hi = (b_end < b1 ? b_end : b1) - b0;
         if (lo >= hi) continue;
       }
       __syncthreads();
@@ -488,6 +496,8 @@ __global__ __launch_bounds__(kThreads, 2) void ring_attn(AttnArgs a) {
         if (seed) {
           score_block(sV + kTileBytes + k_even, sV + kTileBytes + k_odd, qf, sa);
           m = row_max(sa, a.scale_log2);
+          if (tid == kThreads - 64 && a.first_block[1] <= b_begin)
+            count_chunk(a, a.arrival[0], a.need[a.arrival[0]]);  // its block is in LDS
           seed = false;
         }
         score_block(sK + k_even, sK + k_odd, qf, sa);
@@ -502,25 +512,11 @@ __global__ __launch_bounds__(kThreads, 2) void ring_attn(AttnArgs a) {
       // loads are waited for before its LDS stores, and every thread has passed the
       // barrier after the chunk's last stores); prefetches still in flight re-read the
       // chunk's last block and are discarded
-      if (!kSliced && tid == 0) {
-        const uint32_t done =
-            __hip_atomic_fetch_add(a.counters + c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) + 1u;
-        if (done == static_cast<uint32_t>(a.n_units))
-          __hip_atomic_store(a.out_flags + c, a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-      }
+      if (tid == 0) count_chunk(a, c, kSliced ? a.need[c] : a.n_units);
     }
     if (aborted) break;
 
     if constexpr (kSliced) {
-      // A slice counts every chunk at its end, a lane each (it has read its own, and never
-      // reads the others).
-      if (wave == 0)
-        for (int c = lane; c < a.n_chunks; c += 64) {
-          const uint32_t done =
-              __hip_atomic_fetch_add(a.counters + c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) + 1u;
-          if (done == static_cast<uint32_t>(a.n_units))
-            __hip_atomic_store(a.out_flags + c, a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        }
       // Partial results go through to memory (the slices may run on any die); the slice
       // that finishes last reads all of them past the caches and merges them in slice
       // order, so the result does not depend on which slice that was. Layout per slice:

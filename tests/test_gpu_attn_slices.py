@@ -3,6 +3,7 @@ heads): slices of unequal length, slices that begin inside a chunk, chunks no sl
 unit reads, rows whose largest score lies in one slice only, calls in a row on one plan.
 Against plain attention in 64 bits; bf16 weights bound the error at 2e-2 of the result."""
 import math
+import time
 
 import numpy as np
 import pytest
@@ -178,4 +179,37 @@ def test_first_keys_that_score_minus_infinity_count_for_nothing(rows, num_workgr
         scale = float(want.square().mean().sqrt())
         assert (o[:, h].double() - want).abs().max() <= 2e-2 * max(scale, float(want.abs().max()))
         assert (lse[h].double() - torch.logsumexp(s, dim=1)).abs().max() <= 2e-2
+    plan.close()
+
+
+def test_slices_release_a_chunk_before_the_kernel_ends():
+    """The first chunk is one block of two million keys, which eight slices walk for
+    milliseconds: the next call's copy into its rows has to go ahead meanwhile, so two
+    calls return (their copies complete) long before the first kernel ends."""
+    sizes = [64, 64 * 32767]
+    print("attention slices, early release", flush=True)
+    chunks = [(0, 64, 1, 0, 0), (64, sum(sizes), 0, 0, 1)]
+    plan = csg.AttnPlan(1, 1, 128, 128, csg.Schedule.create(chunks, [0, 1]), cfg={"timeout_ms": 1000})
+    assert plan.info.n_units == 8
+    g = torch.Generator(device=DEV).manual_seed(15)
+    q = torch.randn((128, 1, 128), generator=g, device=DEV).to(torch.bfloat16)
+    k = torch.randn((sum(sizes), 1, 128), generator=g, device=DEV).to(torch.bfloat16)
+    v = torch.randn((sum(sizes), 1, 128), generator=g, device=DEV).to(torch.bfloat16)
+    kl, vl = k.clone(), v.clone()
+    o, lse = torch.empty_like(q), torch.empty((1, 128), device=DEV)
+    st, cp = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    plan.ring_attn(q, kl, vl, k, v, o, lse, "overlap", st, cp)   # loads the kernel
+    plan.check()
+    torch.cuda.synchronize()
+    first, kernel_ms = o.clone(), float(plan.kernel_times(1)[0])
+    assert kernel_ms > 1.0
+    torch.cuda.synchronize()
+    t0 = time.perf_counter()
+    plan.ring_attn(q, kl, vl, k, v, o, lse, "overlap", st, cp)
+    plan.ring_attn(q, kl, vl, k, v, o, lse, "overlap", st, cp)
+    assert (time.perf_counter() - t0) * 1e3 < 0.5 * kernel_ms
+    plan.check()
+    torch.cuda.synchronize()
+    assert torch.equal(o, first)
     plan.close()
