@@ -123,16 +123,17 @@ typedef struct {
  *                   order = (key, band, n, m)
  *   group_m         band height of intra_order 1 (0 = 8)
  *   tile_dispatch   1 = workgroups take the next entry of the tile list from an atomic
- *                   ticket; 0 = the same for plans with split tiles, num_workgroups or kernel
- *                   copies, else static as for 2 (with num_workgroups 0, 0 and 1 deal a list
- *                   no longer than the co-resident slots one entry per workgroup, in an
- *                   order chosen for the caches); 2 = static: workgroup w takes entries s, s + G, s + 2G,
- *                   ... with s = (w mod 8) * (G / 8) + w / 8 when G is a multiple of 8
- *                   (else s = w), so that the workgroups of one die (the dispatcher
- *                   deals workgroups to the 8 dies round robin) take consecutive entries;
- *                   with a tail split (all-gather and grouped GEMMs) the units of the
- *                   split tail tiles, which end the list, are taken in order from a
- *                   shared ticket by whichever workgroup is free first
+ *                   ticket; 0 = the same, except that GEMM + reduce-scatter and all-reduce
+ *                   plans with whole tiles, num_workgroups 0 and copies by the engines are
+ *                   dealt statically as for 2; 2 = static: workgroup w takes entries s,
+ *                   s + G, s + 2G, ... with s = (w mod 8) * (G / 8) + w / 8 when G is a
+ *                   multiple of 8 (else s = w), so that the workgroups of one die (the
+ *                   dispatcher deals workgroups to the 8 dies round robin) take consecutive
+ *                   entries; with a tail split (all-gather and grouped GEMMs) the units of
+ *                   the split tail tiles, which end the list, are taken in order from a
+ *                   shared ticket by whichever workgroup is free first. With num_workgroups
+ *                   0, 0 and 1 deal a list no longer than the co-resident slots one entry
+ *                   per workgroup, in an order chosen for the caches
  *   num_workgroups  persistent grid size G (0 = one per co-resident slot, or fewer where
  *                   every entry has a workgroup of its own; those that copy chunks, and
  *                   one that relays the copies' completion to the others, come on top)

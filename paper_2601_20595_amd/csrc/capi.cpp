@@ -379,13 +379,13 @@ csg_status setup_device(csg_plan* p) {
   if (p->cfg.num_workgroups == 0) eo.slots = p->grid - copiers;
   csg::ExecTables et;
   csg::build_exec_tables(p->sched, m, eo, &et);
-  // Several waves of whole tiles, copied by the engines: dealt statically, die by die, unless
-  // tickets are named. The tiles take equal times, so tickets balance nothing, and taking
-  // one costs about a microsecond per tile: gemm-rs 8192 x 4096 x 1792 122 -> 115 us, grouped
-  // 32768 x 1792 x 4096 459 -> 453, all-gather 16384 x 3584 x 8192 778 -> 765. Copy workgroups
-  // keep tickets: they join late.
-  if (!et.one_shot && p->cfg.tile_dispatch == 0 && p->cfg.num_workgroups == 0 && !p->kernel_copies() &&
-      et.ws_slices == 0) {
+  // A producer's several waves of whole tiles, copied by the engines: dealt statically, die
+  // by die, unless tickets are named. No tile waits for an arrival, so they take equal
+  // times, tickets balance nothing, and taking one costs about a microsecond per tile:
+  // gemm-rs 8192 x 4096 x 1792 122 -> 115 us. A consumer's tiles keep tickets: a workgroup
+  // held up by a late chunk would hold up the later tiles of its static share too.
+  if (!et.one_shot && !p->consumer() && p->cfg.tile_dispatch == 0 && p->cfg.num_workgroups == 0 &&
+      !p->kernel_copies() && et.ws_slices == 0) {
     eo.tile_dispatch = 2;
     csg::build_exec_tables(p->sched, m, eo, &et);
   }
