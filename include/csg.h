@@ -139,7 +139,8 @@ typedef struct {
  *                   one that relays the copies' completion to the others, come on top)
  *   copy_engines    SDMA engines the chunk copies are spread over (0 = every engine the
  *                   device offers for device-to-device copies)
- *   timeout_ms      bound on every wait (kernel flag polls, host waits); 0 = 2000
+ *   timeout_ms      bound on every wait (kernel flag polls, host waits); 0 = 2000. A unit's wait
+ *                   for several chunks counts from the last of them that landed
  *   split_k         K-slices per tile (0 = none, or the library's choice, by the shape
  *                   alone, where whole tiles would leave CUs idle; 1 = none): the slices of a tile run on different
  *                   workgroups and the last one to finish adds the fp32 partial sums in slice

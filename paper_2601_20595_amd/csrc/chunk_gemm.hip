@@ -76,7 +76,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, in
 // until its copy in has landed; the producer, until the previous call's copy out of its
 // rows has completed. Returns 1 if a chunk was seen ready for the first time in this
 // workgroup, 0 if all were already known, -1 if the wait gave up (timeout here, or
-// another workgroup's abort). A ready value is a load of over a microsecond away, so each
+// another workgroup's abort). The bound counts from the start or from the last chunk that
+// landed, so chunks that land one after another may each take as long. A ready value is a load of over a microsecond away, so each
 // lane polls a chunk of its own; polled one after another by one thread, the seven
 // 16-row chunks of a 128-row tile held its unit up for 10 us.
 __device__ __forceinline__ int wait_chunks(const GemmArgs& a, int pos, uint32_t* ready_bits, int lane) {
@@ -89,13 +90,14 @@ __device__ __forceinline__ int wait_chunks(const GemmArgs& a, int pos, uint32_t*
     const bool ask = mine && !(ready_bits[c >> 5] & bit);
     if (__builtin_amdgcn_ballot_w64(ask) == 0) continue;
     const int64_t* rp = a.ready[c];
-    const uint64_t t0 = wall_clock64();
+    uint64_t t0 = wall_clock64();
     int64_t v = ask ? load_ready(rp) : 0;
-    while (__builtin_amdgcn_ballot_w64(v != 0) != 0) {
+    uint64_t waiting = __builtin_amdgcn_ballot_w64(v != 0);
+    while (waiting != 0) {
       if (load_flag(&a.diag->abort)) return -1;
       if (wall_clock64() - t0 > a.timeout_ticks) {
         // the first lane still waiting reports its chunk
-        if (lane == __builtin_ctzll(__builtin_amdgcn_ballot_w64(v != 0)) && atomicCAS(&a.diag->timed_out, 0u, 1u) == 0u) {
+        if (lane == __builtin_ctzll(waiting) && atomicCAS(&a.diag->timed_out, 0u, 1u) == 0u) {
           a.diag->chunk = c;
           a.diag->tile = a.raster[pos];
           a.diag->observed = static_cast<uint32_t>(v);
@@ -108,6 +110,9 @@ __device__ __forceinline__ int wait_chunks(const GemmArgs& a, int pos, uint32_t*
       // and faster polling loads that memory channel for no gain
       __builtin_amdgcn_s_sleep(32);
       if (v != 0) v = load_ready(rp);
+      const uint64_t left = __builtin_amdgcn_ballot_w64(v != 0);
+      if (left != waiting) t0 = wall_clock64();
+      waiting = left;
     }
     if (ask) atomicOr(&ready_bits[c >> 5], bit);
     fresh = 1;
@@ -119,15 +124,14 @@ __device__ __forceinline__ int wait_chunks(const GemmArgs& a, int pos, uint32_t*
 // of the relayed list and clears their relay words as they land. The completion values
 // are in host memory, whose reads the device takes one after another (17 ns each): with
 // 224 workgroups polling seven of them each, units started up to 27 us after their
-// chunks had landed; the words in device memory cost about a microsecond. Ends when
-// every chunk has landed, when a wait gave up (the abort flag), or after twice the bound
-// of those waits.
+// chunks had landed; the words in device memory cost about a microsecond. Ends when every
+// chunk has landed, when a wait gave up (the abort flag) or when every unit has ended: the
+// units' waits are bounded, and a unit that is still to start finds its words kept.
 template <int kThreads>
 __device__ __forceinline__ void relay_flags(const GemmArgs& a, int tid) {
   static_assert(kMaxChunks / kThreads <= 32, "a thread's chunks fit a mask");
   uint32_t pending = 0;
   for (int i = tid, j = 0; i < a.n_relay; i += kThreads, ++j) pending |= 1u << j;
-  const uint64_t t0 = wall_clock64();
   while (pending) {
     for (uint32_t left = pending; left; left &= left - 1) {
       const int j = __builtin_ctz(left);
@@ -136,7 +140,7 @@ __device__ __forceinline__ void relay_flags(const GemmArgs& a, int tid) {
         pending &= ~(1u << j);
       }
     }
-    if (load_flag(&a.diag->abort) || wall_clock64() - t0 > 2 * a.timeout_ticks) break;
+    if (load_flag(&a.diag->abort) || load_flag(&a.diag->units_done) >= static_cast<uint32_t>(a.n_tiles)) break;
     __builtin_amdgcn_s_sleep(8);
   }
 }
