@@ -15,24 +15,26 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 CASES = [
-    # rows, heads, kv heads, chunk rows (64 each), local chunks
-    (100, 2, 1, [64] * 13, {0, 1}),                    # 13 blocks: two slices, 6 and 7
-    (1, 4, 2, [64 * 24], {0}),                         # one chunk: every slice inside it
-    (300, 3, 3, [64, 448, 128, 1024, 64, 320], {2}),   # eight slices over uneven chunks
-    (128, 1, 1, [64 * 11], set()),                     # 11 blocks: one slice
-    (4100, 16, 4, [512, 512, 256], {1}),               # more units than slots: not cut
+    # rows, heads, kv heads, chunk rows (multiples of 64), local chunks, slices
+    (100, 2, 1, [64] * 13, {0, 1}, 2),                 # 13 blocks: slices of 6 and 7
+    (1, 4, 2, [64 * 24], {0}, 4),                      # one chunk: every slice inside it
+    (300, 3, 3, [64, 448, 128, 1024, 64, 320], {2}, 5),  # uneven chunks
+    (70, 3, 3, [64, 448, 128, 1024, 64, 1344], {2}, 8),
+    (128, 1, 1, [64 * 11], set(), 1),                  # 11 blocks: not cut
+    (4100, 16, 4, [512, 512, 256], {1}, 1),            # more units than slots: not cut
 ]
 
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "q%d-h%d-kv%d-n%d" % (c[0], c[1], c[2], len(c[3])))
 @pytest.mark.parametrize("spread", [1.0, 8.0])
 def test_sliced_attention_parity(case, spread):
-    rows, H, Hkv, sizes, local = case
+    rows, H, Hkv, sizes, local, slices = case
     print("attention slices", case, spread, flush=True)
     ends = np.cumsum(sizes).tolist()
     chunks = [(e - s, e, 0 if i in local else 1 + i, 0, int(i in local)) for i, (e, s) in enumerate(zip(ends, sizes))]
     order = sorted(range(len(sizes)), key=lambda i: (i not in local, -i))
     plan = csg.AttnPlan(H, Hkv, 128, rows, csg.Schedule.create(chunks, order), cfg={"timeout_ms": 1000})
+    assert plan.info.n_units == (rows + 127) // 128 * H * slices
     g = torch.Generator(device=DEV).manual_seed(7)
     S = ends[-1]
     q = torch.randn((rows, H, 128), generator=g, device=DEV).to(torch.bfloat16)
@@ -72,6 +74,7 @@ def test_slices_of_keys_that_score_minus_infinity_count_for_nothing():
     print("attention slices, -inf scores", flush=True)
     chunks = [(0, sizes[0], 0, 0, 1), (sizes[0], sum(sizes), 1, 0, 0)]
     plan = csg.AttnPlan(H, 1, 128, rows, csg.Schedule.create(chunks, [0, 1]), cfg={"timeout_ms": 1000})
+    assert plan.info.n_units == 8 * H                     # eight slices of six blocks
     g = torch.Generator(device=DEV).manual_seed(9)
     q = torch.randn((rows, H, 128), generator=g, device=DEV).to(torch.bfloat16)
     q[:, :, 0] = q[:, :, 0].abs() + 0.5
@@ -97,7 +100,7 @@ def test_slices_of_keys_that_score_minus_infinity_count_for_nothing():
 SAME = [
     # rows, heads, kv heads, chunk rows, local chunks, arrival order
     (500, 32, 8, [256] * 8, {4, 5}, [4, 5, 6, 7, 0, 1, 2, 3]),   # four slices
-    (300, 3, 3, [64, 448, 128, 1024, 64, 320], set(), [3, 0, 5, 1, 4, 2]),  # eight; the first chunk arrives too
+    (300, 3, 3, [64, 448, 128, 1024, 64, 320], set(), [3, 0, 5, 1, 4, 2]),  # five; the first chunk arrives too
     (64, 2, 1, [64 * 12], {0}, [0]),                             # two slices of one chunk
 ]
 

@@ -16,19 +16,19 @@ if torch.cuda.is_available():
     from gpu_util import bf16_rne_of_f64, out_to_f64, run_ag, run_rs
 
 CASES = [
-    # op, W, S, Q, N, K, dtype, cfg
-    ("ag", 2, 700, 700, 260, 64, "bf16", {}),         # 1-row chunks: 256 per tile, 700 relayed
-    ("ag", 2, 100, 50, 64, 128, "f32", {}),           # lines straddle chunks
-    ("ag", 8, 2, 1, 516, 192, "bf16", {}),            # 16 rows in all, seven remote chunks in one tile
-    ("ag", 4, 64, 1, 260, 128, "bf16", {"copy_backend": "kernel", "copy_workgroups": 5}),
-    ("ag", 2, 4096, 8, 2048, 64, "bf16", {}),         # 256 tiles: no slot left for a relay
-    ("rs", 2, 200, 100, 260, 64, "bf16", {}),         # 128 chunks per tile
+    # op, W, S, Q, N, K, dtype, cfg, workgroups beside those of the units
+    ("ag", 2, 700, 700, 260, 64, "bf16", {}, 8),      # 1-row chunks: 256 per tile, 700 relayed
+    ("ag", 2, 100, 50, 64, 128, "f32", {}, 8),        # lines straddle chunks
+    ("ag", 8, 2, 1, 516, 192, "bf16", {}, 8),         # 16 rows in all, seven remote chunks in one tile
+    ("ag", 4, 64, 1, 260, 128, "bf16", {"copy_backend": "kernel", "copy_workgroups": 5}, 8),
+    ("ag", 2, 4096, 8, 2048, 64, "bf16", {}, 0),      # 256 tiles: no slot left for a relay
+    ("rs", 2, 200, 100, 260, 64, "bf16", {}, 0),      # 128 chunks per tile
 ]
 
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "%s-W%d-S%d-Q%d-N%d-K%d-%s-%d" % (c[:7] + (len(c[7]),)))
 def test_one_shot_bit_exact(case):
-    op, W, S, Q, N, K, dtype, cfg = case
+    op, W, S, Q, N, K, dtype, cfg, others = case
     print("one shot", case, flush=True)
     out = "bf16" if dtype == "bf16" else "f32"
     w = si.Workload(132, "shot", op, M=W * S, N=N, K=K, dtype=dtype, out_dtype=out, dist="int", world=W, rank=W - 1,
@@ -37,6 +37,8 @@ def test_one_shot_bit_exact(case):
     chunks, order = oracle.uniform_schedule(W, W - 1, S, Q, w.order)
     plan = csg.Plan(op, W * S, N, K, dtype, out, csg.Schedule.uniform(W, W - 1, S, Q, w.order),
                     cfg=dict(cfg, timeout_ms=1000))
+    # a workgroup per unit, and eight (one per die) that relay or copy where there are any
+    assert plan.info.num_workgroups == (plan.info.n_units + 7) // 8 * 8 + others
     if op == "ag":
         R = oracle.ag_gemm(d.A.device_array, d.B.device_array, chunks, order)
         for mode in ("overlap", "compute_only", "overlap"):
