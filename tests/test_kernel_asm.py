@@ -145,6 +145,28 @@ def test_library_kernels_have_no_per_lane_barrier_loop(source):
     assert divergent_barrier_loops(asm) == []
 
 
+def wide_stores_with_offset_register(asm: str):
+    """Buffer stores of 12 or 16 bytes per lane whose scalar offset (the operand after the
+    resource) is anything but a literal constant."""
+    bad = []
+    for m in re.finditer(r"^\s*buffer_store_(?:dwordx[34]|format_xyzw?)\s+([^;\n]*)", asm, re.M):
+        operands = [x.strip() for x in m.group(1).split(",")]
+        if len(operands) < 4 or not re.fullmatch(r"-?(?:0x[0-9a-f]+|\d+)", (operands[3].split() or [""])[0]):
+            bad.append(m.group(0).strip())
+    return bad
+
+
+def test_checker_flags_every_offset_register_of_a_wide_store():
+    bad = ["buffer_store_dwordx4 v[0:3], v4, s[8:11], s20 offen", "buffer_store_dwordx4 v[0:3], v4, s[8:11], s20",
+           "buffer_store_dwordx3 v[0:2], v4, s[8:11], vcc_lo offen sc0 sc1", "buffer_store_dwordx4 v[0:3], off, s[8:11], m0",
+           "buffer_store_dwordx4 v[0:3], v4, s[8:11], ttmp3 offen offset:16",
+           "buffer_store_dwordx4 a[0:3], v4, s[8:11], exec_hi offen", "buffer_store_dwordx4 v[0:3], v4, s[8:11]"]
+    good = ["buffer_store_dwordx4 v[0:3], v4, s[8:11], 0 offen", "buffer_store_dwordx4 v[0:3], v4, s[8:11], 0",
+            "buffer_store_dwordx3 v[0:2], off, s[8:11], 0 offset:4080 sc0 sc1 ; note, s3",
+            "buffer_store_dwordx2 v[0:1], v4, s[8:11], s20 offen", "buffer_load_dwordx4 v[0:3], v4, s[8:11], s20 offen"]
+    assert wide_stores_with_offset_register("".join("\t%s\n" % x for x in bad + good)) == bad
+
+
 @pytest.mark.parametrize("source", KERNEL_SOURCES)
 def test_no_wide_store_with_a_scalar_offset_register(source):
     """A buffer store of 12 or 16 bytes per lane reads its data registers for a few cycles
@@ -152,6 +174,5 @@ def test_no_wide_store_with_a_scalar_offset_register(source):
     store's scalar offset is no register; with one, results were replaced by the next
     address now and then. Every such store must therefore have none."""
     asm = device_asm(os.path.join(ROOT, "paper_2601_20595_amd", "csrc", source))
-    wide = re.findall(r"^\s*(buffer_store_dwordx[34] .*)$", asm, re.M)
-    assert source != "chunk_gemm.hip" or wide
-    assert [w for w in wide if re.search(r"\], s\d+ ", w)] == []
+    assert re.search(r"^\s*buffer_store_dwordx4 ", asm, re.M)
+    assert wide_stores_with_offset_register(asm) == []
