@@ -141,11 +141,14 @@ typedef struct {
  *                   device offers for device-to-device copies)
  *   timeout_ms      bound on every wait (kernel flag polls, host waits); 0 = 2000. A unit's wait
  *                   for several chunks counts from the last of them that landed
- *   split_k         K-slices per tile (0 = none, or the library's choice, by the shape
- *                   alone, where whole tiles would leave CUs idle; 1 = none): the slices of a tile run on different
- *                   workgroups and the last one to finish adds the fp32 partial sums in slice
- *                   order, so the result depends on split_k but not on timing; a larger value
- *                   shortens the work left after the last chunk lands (and the first emission)
+ *   split_k         K-slices per tile (1 = none; 0 = none, or, where whole tiles would leave
+ *                   CUs idle, the library's choice, which depends on the shape, the device's
+ *                   CUs, the operation and the workgroups that copy chunks): the slices of a
+ *                   tile run on different workgroups and the last one to finish adds the fp32
+ *                   partial sums in slice order, so the result depends on the number of slices
+ *                   but not on timing (1 gives the same bits with every copy backend); a larger
+ *                   value shortens the work left after the last chunk lands (and the first
+ *                   emission)
  *   tail_split      K-slices for the tiles on the overlap's critical path: the tiles that
  *   tail_chunks     read one of the tail_chunks last-arriving chunks (AG, grouped) or write
  *                   one of the tail_chunks first-emitted chunks (RS); 0 = none. Slices are
@@ -209,7 +212,8 @@ typedef struct {
     int32_t nnz;            /* sum over tiles of the chunks each tile touches */
     int32_t n_tiles_n;      /* tiles along N */
     int32_t num_workgroups; /* persistent grid actually used (0 on a host-only plan) */
-    int32_t bm, bn, bk;     /* tile shape actually used */
+    int32_t bm, bn, bk;     /* tile shape of the map; a default plan's kernel may run each tile
+                               as several smaller ones or K-slices (csg_plan_cfg) */
     int32_t n_units;        /* work units of the execution list (0 on a host-only plan) */
 } csg_plan_info;
 
@@ -220,7 +224,8 @@ typedef struct {
  * that was not the last), and the shader-clock cycles in between, so that
  * cycles / (t_end - t_start) * 100 MHz is the clock the unit ran at. */
 typedef struct {
-    int32_t raster;         /* raster id of the tile */
+    int32_t raster;         /* raster id of the tile (of the plan's tile that holds it, where
+                               the kernel runs smaller ones: several units then name it) */
     int32_t slice;          /* K-slice index */
     int32_t n_slices;       /* K-slices of the tile (1 = not split) */
     int32_t xcd;            /* die the workgroup ran on */
@@ -364,14 +369,15 @@ csg_status csg_ag_gemm(csg_plan* p, void* a_landing, const void* a_staging, cons
  * the library, 18 MiB per device, which each device the library runs on holds from the
  * library's load until the process ends. The call allocates nothing (no hipMalloc,
  * hipFree or allocating library routine); it queues a table upload when the schedule,
- * shape or dtypes differ from the previous call's on the device, then a prologue and
- * the kernel, all on `stream` (a hipStream_t of `device`), and returns.
+ * shape, dtypes or copy_workgroups differ from the previous call's on the device, then a
+ * prologue and the kernel, all on `stream` (a hipStream_t of `device`), and returns.
  * Arguments as for csg_plan_create + csg_ag_gemm: `s` (host; not kept after the call)
  * covers exactly M rows; a_landing (M x K, local rows in place), a_staging (same
  * layout, the remote rows), b_nk (N x K), c (M x N) are device buffers of `device`,
  * 16-byte aligned; tiles are 256 x 256 x 64 (bf16 input; smaller ones and K-slices where
  * those would leave CUs idle, as for a plan) or 64 x 64 x 16 (f32, also in K-slices),
- * dispatched per die with stealing. copy_workgroups: workgroups that move the chunks
+ * dispatched per die with stealing, or one per workgroup where they are no more than the
+ * slots that copy_workgroups leaves. copy_workgroups: workgroups that move the chunks
  * (0 = 16). Modes as for csg_ag_gemm (compute-only: a_landing already holds every row;
  * copy-only: the copy workgroups alone run).
  * Limits: at most 4096 chunks, 16384 tiles, 32768 (tile, remote chunk) pairs and 16384
@@ -465,8 +471,9 @@ csg_status csg_attn_plan_create(int32_t n_heads, int32_t n_kv_heads, int32_t hea
  * one completion signal as the chunk's ready flag) once the previous call's kernel
  * has finished reading those rows, and returns when the copies have completed
  * (copy-only mode: once they are issued, as for csg_ag_gemm). Each
- * work unit (one head, 128 query rows; where those would leave slots idle, a slice of the
- * keys of one) consumes the chunks in arrival order, waiting for each once. Compute-only: the landing buffers must already hold every row. */
+ * work unit (one head, 128 query rows; where those would leave slots idle and
+ * num_workgroups is 0, a slice of the keys of one) consumes the chunks in arrival order,
+ * waiting for each once. Compute-only: the landing buffers must already hold every row. */
 csg_status csg_ring_attn(csg_plan* p, const void* q, void* k_landing, void* v_landing,
                          const void* k_staging, const void* v_staging, void* o, void* lse,
                          csg_mode mode, void* compute_stream, void* copy_stream);

@@ -22,8 +22,9 @@
 //         through a ring of K stages: two for 256 x 256 tiles, three for the smaller
 //         tiles, whose stages take fewer MFMAs to consume than a load takes to land;
 //         LDS rows are 128 bytes with an XOR swizzle of their 16-byte
-//         vectors that keeps both the DMA writes and the ds_read_b128 fragment reads
-//         free of bank conflicts.
+//         vectors that keeps the DMA writes and the ds_read_b128 fragment reads of
+//         32 x 32 MFMAs free of bank conflicts; those of 16 x 16 ones still conflict two
+//         ways (SQ_LDS_BANK_CONFLICT is half of SQ_LDS_IDX_ACTIVE in every such loop).
 //   fp32: 256 threads = 2 x 2 waves; v_mfma_f32_32x32x2_f32, tiles by the same DMA and
 //         swizzle in a three-stage ring.
 // The MFMA takes the B fragment as its first operand, so each lane ends up with runs
@@ -520,9 +521,13 @@ struct Bf16Loop {
 // Both waits leave the newest 8 loads in flight:
 //   phase 0 of step t issues A1(t + 1) and needs A1(t), which 6 + 2 loads follow;
 //   phase 1 of step t issues A0, B0, B1 (t + 2) and needs A0, B0, B1 (t + 1): 2 + 6.
-// Bound: the chip's power. A step takes about 2400 cycles for 2048 of MFMA issue (2600
-// with all eight waves in step, 2x2 halves per phase; 2570 with a plain double buffer
-// and 32 x 32 x 16 MFMAs), and the clock falls to 1.6-1.7 GHz as the utilisation rises.
+// Bound: the matrix cores and the clock that the chip's power leaves them. A step takes
+// 2380 cycles for 2048 of MFMA issue where all tiles run at once (unit trace, 8192 x 1792, K
+// 2048 to 8192), 2400-2530 over several waves of tiles (16384 x 3584; 2600 with all eight
+// waves in step, 2x2 halves per phase; 2570 with a plain double buffer and 32 x 32 x 16
+// MFMAs), and the clock falls to 1.66-1.8 GHz (2.2 GHz in a 0.1 ms kernel). Counters of
+// 16384 x 3584 x 8192: matrix cores busy 66 % of all SIMD cycles, 78 % of those of busy
+// CUs; the fragment reads' two-way bank conflicts pass under the other group's MFMAs.
 // 16384 x 3584 x 8192: 835 -> 722 us (1152 -> 1333 TFLOP/s); 8192 x 8192 x 8192: 974 ->
 // 857; 8192 x 1792 x 4096: 121 -> 114; 8192 x 2048 x 8192: 228 -> 212 us. Four phases of 16
 // MFMAs per step, the halves loaded one per phase: 732, 1053, 115 and 217 us.
@@ -1051,8 +1056,9 @@ __global__ __launch_bounds__(Loop::THREADS, 1) void chunk_gemm(GemmArgs a) {
   xcd %= kXcdLists;
   uint32_t units = 0;  // work units this workgroup executed (the host checks the total)
 
-  // Workgroups 0 .. copy_wgs - 1 move the chunks, then take tiles too. The dispatcher
-  // starts workgroups in index order, so they are running whenever a tile waits.
+  // Workgroups 0 .. copy_wgs - 1 move the chunks, then take tiles too (where every unit has
+  // a workgroup of its own, they end). The dispatcher starts workgroups in index order, so
+  // they are running whenever a tile waits.
   const int n_copiers = a.copy_wgs < static_cast<int>(gridDim.x) ? a.copy_wgs : static_cast<int>(gridDim.x);
   if (a.n_copy_items > 0 && static_cast<int>(blockIdx.x) < n_copiers)
     copy_chunks<kThreads>(a, tid, static_cast<int>(blockIdx.x), n_copiers);
@@ -1147,8 +1153,8 @@ __global__ __launch_bounds__(Loop::THREADS, 1) void chunk_gemm(GemmArgs a) {
       for (int j = 0; j < NI; ++j) acc[i][j] = f32x16{};
     Loop::run(lds, g, acc, wave, lane);
     // Output run r = (i * NI + j) * 4 + q of this thread: accumulator elements
-    // 4q..4q+3 of block (i, j), i.e. output row (i * 32 + lane % 32) and columns
-    // (j * 32 + 8q + 4 * (lane / 32) + 0..3) of the wave's sub-tile.
+    // 4q..4q+3 of block (i, j), i.e. output row lane_row + run_row(i, q) and columns
+    // lane_col + run_col(j, q) + 0..3 of the wave's sub-tile.
     constexpr int kRuns = MI * NI * 4;
     constexpr int kOutBytes = kOutBf16 ? 2 : 4;
     // The producer's C goes straight to memory (system-coherent stores, sc0 sc1): the
@@ -1361,8 +1367,8 @@ __global__ __launch_bounds__(Loop::THREADS, 1) void chunk_gemm(GemmArgs a) {
       // finishes its tile last adds all of them in slice order (so the result does not
       // depend on which slice finished when) and writes the output from those sums.
       constexpr int kSliceBytes = kRuns * kThreads * 16;  // one slice of one tile
-      // slice layout: run r of thread t at byte (r * kThreads + t) * 16; addressed
-      // through a buffer resource so the per-run offset is a scalar operand
+      // slice layout: run r of thread t at byte (r * kThreads + t) * 16; the loads' per-run
+      // offset is a scalar operand, the stores' a part of the lane's (see store_b128)
       const __amdgpu_buffer_rsrc_t rsW = make_rsrc(a.ws + static_cast<int64_t>(td.slot) * (kSliceBytes / 4),
                                                    static_cast<int64_t>(nslices) * kSliceBytes);
       int toff = tid * 16;

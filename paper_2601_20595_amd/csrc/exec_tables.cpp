@@ -167,6 +167,11 @@ void build_exec_tables(const Schedule& s, const TileMap& m, const ExecOptions& o
 //   2048 x 1792 x 4096: 256 x 256 77.5 (79), in two slices 58.6 (56), 128 x 128 39.6 (39)
 //   4096 x 1792 x 4096: 256 x 256 79.0 (79), in two slices 69.3 (68); 128 x 128 93.1 (448
 //                       tiles, two waves)
+// fp32, 64 x 64 tiles (estimates run low, alike for every number of slices):
+//   256 x 256 x 2048:   whole 45.3 (36), in two slices 28.2 (22), four 18.4 (17), eight 15.4 (15)
+//   128 x 1792 x 1024:  whole 26.8 (21), in two slices 19.6 (15), four 15.6 (13)
+//   1024 x 512 x 4096:  whole 87.3 (68), in two slices 53.2 (41)
+//   256 x 256 x 256:    whole 12.3 (10), in two slices 11.6 (10), four 10.0 (10)
 // 256 x 256 tiles run whole wave after whole wave; the small ones, whose operands cost
 // twice the traffic per product, only where all of them run at once.
 Geometry choose_geometry(bool bf16, const std::vector<int64_t>& group_rows, int64_t N, int64_t K, int32_t slots,
