@@ -216,3 +216,35 @@ def test_slices_release_a_chunk_before_the_kernel_ends():
     torch.cuda.synchronize()
     assert torch.equal(o, first)
     plan.close()
+
+
+@pytest.mark.parametrize("num_workgroups", [1, 24, 63, 64, 71, 72, 100, 504, 512])
+def test_units_of_a_named_grid_are_spread_over_the_dies(num_workgroups):
+    """64 units on grids of fewer, as many and more workgroups: the same bits, and a grid
+    larger than the units is no slower than one of as many (the units of a 512-workgroup
+    grid once ran on one die: 1.4 times the time)."""
+    rows, H, S = 100, 64, 4096
+    print("attention, named grid", num_workgroups, flush=True)
+    g = torch.Generator(device=DEV).manual_seed(17)
+    q = torch.randn((rows, H, 128), generator=g, device=DEV).to(torch.bfloat16)
+    k = torch.randn((S, H, 128), generator=g, device=DEV).to(torch.bfloat16)
+    v = torch.randn((S, H, 128), generator=g, device=DEV).to(torch.bfloat16)
+    st, cp = torch.cuda.Stream(), torch.cuda.Stream()
+    out, ms = [], []
+    for n in (64, num_workgroups):
+        plan = csg.AttnPlan(H, H, 128, rows, csg.Schedule.create([(0, S, 0, 0, 1)], [0]),
+                            cfg={"timeout_ms": 1000, "num_workgroups": n})
+        assert plan.info.n_units == 64
+        o, lse = torch.full_like(q, float("nan")), torch.empty((H, rows), device=DEV)
+        torch.cuda.synchronize()
+        for _ in range(30):
+            plan.ring_attn(q, k, v, k, v, o, lse, "compute_only", st, cp)
+        plan.check()
+        torch.cuda.synchronize()
+        out.append((o, lse))
+        ms.append(float(np.median(plan.kernel_times(20))))
+        plan.close()
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    print("ms", ms, flush=True)
+    if num_workgroups >= 64:
+        assert ms[1] <= 1.2 * ms[0]
