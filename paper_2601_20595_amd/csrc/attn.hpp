@@ -41,6 +41,8 @@ struct AttnArgs {
   const int32_t* first_block; // [n_chunks + 1] by arrival position: key blocks of the chunks before it
   const int32_t* need;        // [n_chunks] by chunk id: units that read it, 0 if it is local (slices > 1)
   const int64_t* const* ready;  // per chunk id: 0 once its keys and values have landed
+  int64_t* const* relay;        // [n_chunks]: word in device memory that a unit which saw the value 0 clears
+                                // (a local chunk's: a word that reads 0)
   uint32_t* counters;         // per chunk id: units done reading it
   uint32_t* out_flags;        // per chunk id: the call number once every unit has read it
   uint32_t* ticket;           // [kXcdLists] work-unit tickets, one per die's range of units
@@ -53,6 +55,8 @@ struct AttnArgs {
   uint32_t* next_counters;
   DeviceDiag* next_diag;
   uint32_t* next_slot_count;  // (null where slices is 1)
+  int64_t* next_relay;        // relay words of the next call's set, set to 1
+  int32_t n_relay;            // remote chunks
 };
 
 // A slice's partial results: per thread its 64 output accumulators, its row's reference

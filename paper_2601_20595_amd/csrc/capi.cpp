@@ -1018,6 +1018,8 @@ csg_status setup_attn_device(csg_plan* p) {
     state.add_zeros(&p->d_slot_count, 2 * static_cast<size_t>(whole) * 4);
     CSG_HIP(hipMalloc(&p->d_ws, static_cast<size_t>(p->n_units) * csg::kAttnPartBytes));
   }
+  p->n_relay = static_cast<int32_t>(p->remote_order.size());
+  if (p->n_relay > 0) state.add_zeros(&p->d_relay, 2 * static_cast<size_t>(p->n_relay) * sizeof(int64_t));
   if ((st = state.commit(&p->d_state)) != CSG_OK) return st;
   CSG_HIP(hipHostMalloc(&p->h_out_flags, nflag * 4, hipHostMallocMapped | hipHostMallocCoherent));
   std::memset(p->h_out_flags, 0, nflag * 4);
@@ -1036,6 +1038,9 @@ csg_status setup_attn_device(csg_plan* p) {
       ptrs[p->remote_order[i]] = vp;
     }
     tables.add(&p->d_ready[set], ptrs);
+    std::vector<int64_t*> words(p->n_chunks(), p->d_zero);
+    for (int32_t i = 0; i < p->n_relay; ++i) words[p->remote_order[i]] = p->relay(set) + i;
+    tables.add(&p->d_relay_dst[set], words);
   }
   if ((st = setup_join(p, &tables)) != CSG_OK) return st;
   if ((st = tables.commit(&p->d_tables)) != CSG_OK) return st;
@@ -1077,6 +1082,9 @@ csg_status launch_attn(csg_plan* p, const void* q, const void* k, const void* v,
   a.first_block = p->d_first_block;
   a.need = p->d_need;
   a.ready = p->d_ready[set];
+  a.relay = p->d_relay_dst[set];
+  a.next_relay = p->relay(next);
+  a.n_relay = p->n_relay;
   a.counters = p->counters(set);
   a.out_flags = p->h_out_flags_dev;
   a.ticket = p->ticket(set);
