@@ -1152,6 +1152,11 @@ __global__ __launch_bounds__(Loop::THREADS, 1) void chunk_gemm(GemmArgs a) {
 #pragma unroll
       for (int j = 0; j < NI; ++j) acc[i][j] = f32x16{};
     Loop::run(lds, g, acc, wave, lane);
+    // Every load of this unit has landed (the main loop ends on a wait and a barrier): count
+    // the unit against the remote chunks it read, so that the last reader of a chunk lets the
+    // next call's copies overwrite its rows, while this call's output is still to be stored
+    // (counted after the stores, calls in a row of 8416 x 1744 x 640 took 68 us instead of 64).
+    if (!kProducer && wave == 0 && a.n_copy_items == 0) count_chunks(a, pos, lane);
     // Output run r = (i * NI + j) * 4 + q of this thread: accumulator elements
     // 4q..4q+3 of block (i, j), i.e. output row lane_row + run_row(i, q) and columns
     // lane_col + run_col(j, q) + 0..3 of the wave's sub-tile.
@@ -1476,13 +1481,8 @@ __global__ __launch_bounds__(Loop::THREADS, 1) void chunk_gemm(GemmArgs a) {
       }
       if (wave == 0) count_chunks(a, pos, lane);
     }
-    if (!kProducer && wave == 0) {
-      // every load of this unit has landed (the main loop ends on a wait and a barrier):
-      // count the unit against the remote chunks it read, so that the last reader of a
-      // chunk lets the next call overwrite its rows. After the output's stores, which
-      // the counters' round trip would otherwise hold up.
-      count_chunks(a, pos, lane);
-    }
+    // (no copy of the next call waits for chunks that the kernel itself moves)
+    if (!kProducer && wave == 0 && a.n_copy_items > 0) count_chunks(a, pos, lane);
     if (a.trace && tid == 0) {
       a.trace[kTraceWords * pos + 2] = wall_clock64();
       a.trace[kTraceWords * pos + 5] = clock64();
