@@ -112,7 +112,7 @@ __device__ __forceinline__ int wait_chunks(const GemmArgs& a, int pos, uint32_t*
       __builtin_amdgcn_s_sleep(32);
       if (v != 0) v = load_ready(rp);
       const uint64_t left = __builtin_amdgcn_ballot_w64(v != 0);
-      if (left != waiting) t0 = wall_clock64();
+      if (left != waiting && left != 0) t0 = wall_clock64();
       waiting = left;
     }
     if (ask) atomicOr(&ready_bits[c >> 5], bit);
