@@ -247,10 +247,10 @@ def test_units_of_a_named_grid_are_spread_over_the_dies(num_workgroups):
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
     print("ms", ms, flush=True)
     if num_workgroups >= 64:
-        assert ms[1] <= 1.2 * ms[0]
+        assert ms[1] <= 1.3 * ms[0]
 
 
-@pytest.mark.parametrize("case,bound", [((1230, 32, 8, 640), 1.35), ((640, 32, 8, 1280), 1.8)], ids=["uncut", "cut"])
+@pytest.mark.parametrize("case,bound", [((1230, 32, 8, 640), 1.4), ((640, 32, 8, 1280), 1.8)], ids=["uncut", "cut"])
 def test_waiting_units_do_not_hold_up_the_copies_they_wait_for(case, bound):
     """Calls in a row on one landing buffer, half of the keys copied. Every unit reaches the
     remote half at once; when all of them polled the copies' completion values, which lie in

@@ -16,7 +16,7 @@ def _call(cfg, delays_us, S=16, K=128):
     dtype = "f32" if K == 64 else "bf16"
     t = torch.float32 if K == 64 else torch.bfloat16
     sched = csg.Schedule.uniform(W, 0, S, 1, "ring")
-    plan = csg.Plan("ag", W * S, N, K, dtype, dtype, sched, cfg=dict(cfg, timeout_ms=60))
+    plan = csg.Plan("ag", W * S, N, K, dtype, dtype, sched, cfg=dict(cfg, timeout_ms=200))
     plan.set_copy_delays(delays_us)
     g = torch.Generator(device=DEV).manual_seed(3)
     a = torch.randint(-2, 3, (W * S, K), generator=g, device=DEV).to(t)
@@ -37,7 +37,7 @@ def _call(cfg, delays_us, S=16, K=128):
                          ids=["relay", "static", "f32"])
 def test_chunks_that_land_one_after_another_are_waited_for(cfg, S, K):
     print("wait bound", cfg, S, K, flush=True)
-    c, want, plan = _call(cfg, [40000.0] * 5, S, K)     # the last lands after 200 ms
+    c, want, plan = _call(cfg, [120000.0] * 5, S, K)    # the last lands after 600 ms
     assert torch.equal(c, want)
     plan.close()
 
@@ -46,7 +46,7 @@ def test_chunks_that_land_one_after_another_are_waited_for(cfg, S, K):
 def test_a_chunk_that_stays_away_ends_the_call(cfg):
     print("wait bound, late", cfg, flush=True)
     with pytest.raises(csg.CsgError) as e:
-        _call(cfg, [40000.0, 40000.0, 150000.0, 0.0, 0.0])
+        _call(cfg, [120000.0, 120000.0, 500000.0, 0.0, 0.0])
     assert e.value.status == csg.CSG_ERR_TIMEOUT
     _, order = csg.Schedule.uniform(6, 0, 16, 1, "ring").get()
     assert e.value.diag.chunk in [x for x in order if x != 0][2:]
