@@ -141,10 +141,11 @@ struct csg_plan {
   int32_t unit_wg0 = 0;                // one-shot: workgroups that only copy or relay, before those of the units
   // One-shot consumers with slots to spare: workgroup 0 relays the copies' completion
   // values into words in device memory. n_relay chunks (remote_order), words by call parity.
+  // Attention: a few units do, for every remote chunk.
   int32_t n_relay = 0;
   int64_t* d_relay = nullptr;               // [2][n_relay]
   const int64_t** d_relay_src[2] = {nullptr, nullptr};  // [n_relay] completion values
-  int64_t** d_relay_dst[2] = {nullptr, nullptr};        // [n_relay] relay words
+  int64_t** d_relay_dst[2] = {nullptr, nullptr};        // [n_relay] relay words (attention: [n_chunks], d_zero if local)
   const int64_t** d_ready_relay[2] = {nullptr, nullptr};  // [n_chunks] what the units poll
   uint64_t* d_trace = nullptr;         // per-unit trace words (cfg.trace; own allocation)
   std::vector<csg::TileDesc> units;    // host copy of the execution list
